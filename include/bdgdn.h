@@ -231,9 +231,10 @@ int bdgdn_fwd_train_views(const bdgdn_fwd_desc_t *desc,
  * clean seed state (fp16), the part of the clean state gradient at the block's start that
  * does not depend on the gradient at its end (fp16; overwritten by the gradient at the
  * block's end once the reverse scan has read it), the block's U K (32 x d_k fp16) and
- * gamma_n; plus 2.3 KB for the range pass.  Per-step shapes: the clean state before every
- * eighth block of every chain (fp32) and eight block-start states per (chain, 16-column
- * tile) (fp32).  0 for a descriptor it would reject. */
+ * gamma_n; plus 2.3 KB for the range pass.  Per-step shapes: two states per (block, v-head)
+ * (fp32), at least (and where that is over 2 GiB, only) what the serial schedule needs: the
+ * clean state before every eighth block of every chain (fp32) and eight block-start states
+ * per (chain, 16-column tile) (fp32).  0 for a descriptor it would reject. */
 size_t bdgdn_bwd_train_workspace(const bdgdn_fwd_desc_t *desc);
 
 /* Bytes of device workspace bdgdn_bwd_train (and bdgdn_bwd_train_views) needs when run in
@@ -279,13 +280,14 @@ size_t bdgdn_bwd_train_workspace_segmented(const bdgdn_fwd_desc_t *desc, const i
  *                        more, smaller launches); BDGDN_ERR_WORKSPACE if none fits
  * Every gradient row is overwritten.  bf16 inputs with d_k = d_v = 128 and blocks of at
  * most 32 positions run the block-form kernels; fp32 inputs (blocks of at most 32), d_k or
- * d_v of 64, and bf16 blocks of 33 .. 64 positions run the per-step fp32 backward (one
- * wave per (chain, 16-column tile) walking the steps backwards from strided clean
- * checkpoints; at most 512 packed documents and four views); anything else is
- * BDGDN_ERR_UNSUPPORTED.  The block-form kernels are deterministic, grouped value heads
- * included (dq, dk of a q/k head summed over its v-heads in a fixed order).  The per-step
- * backward sums dq, dk, dg and dbeta over its column tiles with floating-point atomics
- * (summation order not fixed).
+ * d_v of 64, and odd bf16 blocks of 33 .. 63 positions run the per-step fp32 backward (at
+ * most 512 packed documents and four views): all blocks in parallel between two serial walks
+ * of the clean state and its gradient, or, with less workspace than two states per (block,
+ * v-head), one wave per (chain, 16-column tile) walking the steps backwards from strided
+ * clean checkpoints.  Anything else is BDGDN_ERR_UNSUPPORTED.  The block-form kernels and the
+ * parallel per-step ones are deterministic, grouped value heads included (dq, dk of a q/k
+ * head summed over its v-heads in a fixed order).  The serial per-step walk sums dq, dk, dg
+ * and dbeta over its column tiles with floating-point atomics (summation order not fixed).
  * Range: do, don and the state gradients enter the products as fp16 operands.  Every result
  * is linear in do, don and dht, so the call first finds the largest |entry| of do, don (of
  * every view) and dht on the device, multiplies them by the power of two sigma that puts it

@@ -729,17 +729,24 @@ static SegLayout seg_layout(const bdgdn_fwd_desc_t *d, const SegPlan &p)
     return l;
 }
 
-// Shapes outside the block-form kernels run the per-step fp32 backward (bwd_generic.hip).
+// Shapes outside the block-form kernels run the per-step fp32 backward: parallel over blocks
+// (bwd_steps.hip) given its two states per (block, v-head), else, with less workspace, the
+// serial walk from strided checkpoints (bwd_generic.hip).
 static bool bwd_generic_ok(const bdgdn_fwd_desc_t *d, int n_views)
 {
     return !bwd_shape_ok(d) && d->num_seqs <= kMaxOrder &&
            bwd_generic_supported(d->dtype == BDGDN_F32, d->d_k, d->d_v, d->block, n_views);
 }
-static size_t bwd_generic_bytes(const bdgdn_fwd_desc_t *d)
+static size_t bwd_walk_bytes(const bdgdn_fwd_desc_t *d)
 {
     const int nseq = d->num_seqs > 0 ? d->num_seqs : d->batch;
     return bwd_generic_workspace(nseq, total_blocks(d), d->h_v, d->d_k, d->d_v);
 }
+static size_t bwd_steps_bytes(const bdgdn_fwd_desc_t *d)
+{
+    return bwd_steps_workspace(total_blocks(d), d->h_v, d->d_k, d->d_v);
+}
+static size_t bwd_generic_bytes(const bdgdn_fwd_desc_t *d) { return std::max(bwd_walk_bytes(d), bwd_steps_bytes(d)); }
 
 size_t bdgdn_bwd_train_workspace(const bdgdn_fwd_desc_t *desc)
 {
@@ -795,7 +802,9 @@ static int bwd_impl(const bdgdn_fwd_desc_t *desc, const void *q, const void *k, 
     SegPlan plan;
     bool segmented = false;
     if (workspace_bytes < need) {
-        if (generic) return BDGDN_ERR_WORKSPACE;
+        if (generic && workspace_bytes < bwd_walk_bytes(desc)) return BDGDN_ERR_WORKSPACE;
+    }
+    if (workspace_bytes < need && !generic) {
         int K = 2;
         for (;; ++K) {
             if (!seg_plan(desc, cu_seqlens_host, K, false, plan)) return BDGDN_ERR_WORKSPACE;
@@ -825,7 +834,10 @@ static int bwd_impl(const bdgdn_fwd_desc_t *desc, const void *q, const void *k, 
         c.d_k = desc->d_k; c.d_v = desc->d_v;
         c.scale = desc->scale;
         c.workspace = workspace;
-        const hipError_t e = launch_bwd_generic(desc->dtype == BDGDN_F32, desc->out_dtype == BDGDN_F32, c, strm);
+        const size_t steps = bwd_steps_bytes(desc);
+        const bool f32_in = desc->dtype == BDGDN_F32, f32_out = desc->out_dtype == BDGDN_F32;
+        const hipError_t e = steps > 0 && workspace_bytes >= steps ? launch_bwd_steps(f32_in, f32_out, c, strm)
+                                                                   : launch_bwd_generic(f32_in, f32_out, c, strm);
         return e == hipSuccess ? BDGDN_OK : BDGDN_ERR_LAUNCH;
     }
     unsigned char *ws = static_cast<unsigned char *>(workspace);

@@ -94,6 +94,11 @@ struct GenBwdCall {
 size_t bwd_generic_workspace(int n_seq, long total_blocks, int h_v, int dk, int dv);
 bool bwd_generic_supported(bool f32_in, int dk, int dv, int L, int n_views);
 hipError_t launch_bwd_generic(bool f32_in, bool f32_out, const GenBwdCall &c, hipStream_t s);
+// The same gradients parallel over blocks (bwd_steps.hip), with two fp32 states per (block,
+// v-head) of workspace; bwd_steps_workspace is 0 where that is more than kStepsMaxBytes.
+constexpr size_t kStepsMaxBytes = (size_t)2 << 30;
+size_t bwd_steps_workspace(long total_blocks, int h_v, int dk, int dv);
+hipError_t launch_bwd_steps(bool f32_in, bool f32_out, const GenBwdCall &c, hipStream_t s);
 size_t bwd_block_lds();
 // The backward of a's two streams, plus n_more further noisy views seeded from the same clean
 // states (their seed gradients summed into the clean state gradient).  a.L is the clean

@@ -1,8 +1,10 @@
 // bwd_generic.hip -- the per-step backward of the two-stream training forward (Appendix
 // "Backward primitives": eq. per-step-bwd for each step, the noisy block-end readout
 // backward eq. noisy-readout-bwd, and the block-level chain rule eq. dh-block-recursion),
-// in fp32, for the shapes outside the block-form backward of bwd_kernels.hip: fp32 inputs,
-// d_k or d_v of 64, blocks of 33 to 64 positions.
+// in fp32, for the shapes outside the block-form backward of bwd_kernels.hip (fp32 inputs,
+// d_k or d_v of 64, odd blocks of 33 to 63 positions), as one serial walk per chain: the
+// schedule for a caller whose workspace is below the two states per (block, v-head) that the
+// block-parallel one of bwd_steps.hip takes.
 //
 // Forward step t (column by column of the d_k x d_v state, alpha = exp g):
 //     u = v - alpha S^T k,   S' = alpha S + beta k u^T,   clean o = s S'^T q.

@@ -1,0 +1,843 @@
+// bwd_steps.hip -- the per-step fp32 backward of the two-stream training forward, parallel
+// over blocks (Appendix "Backward primitives": eq. per-step-bwd, eq. noisy-readout-bwd,
+// eq. dh-block-recursion), for the shapes outside the block-form backward of
+// bwd_kernels.hip: fp32 inputs, d_k or d_v of 64, odd blocks of 33 to 63 positions.
+//
+// Forward step i (alpha = exp g):  u = v - alpha S^T k,  S' = alpha S + beta k u^T.
+// Backward from the gradient dS' of S' (a clean step first adds s q do^T to it):
+//     w = dS'^T k,  dv = beta w,  dbeta = w . u,  dk = beta (dS' u - alpha S w),
+//     dS = alpha (dS' - beta k w^T),  clean: dq = s S' do.
+// Neither recurrence needs the other's states: S runs forwards from k, v, gates; dS runs
+// backwards from k, q, do, gates and the noisy seeds' gradients.  So only those two walks
+// are serial, and everything else is done for all blocks at once:
+//   1. states: the clean state before every block (one wave per 4 columns of a chain);
+//   2. noisy blocks in parallel from their seeds: every gradient, and the seed's gradient;
+//   3. reverse: the gradient dh of the state at every block's end (one wave per 4 columns),
+//      stored over the seed gradients it has consumed;
+//   4. clean blocks in parallel from the state at their start and dh.
+// A block (2, 4) is three walks over its positions: forwards for u (and the clean dq),
+// backwards for w, dv, dbeta and the first part of dk, forwards again for the second part of
+// dk.  The gate gradient needs no further state: with dg_i = <dS^_i, alpha S_(i-1)> (dS^ the
+// gradient of the decayed state) one step gives
+//     dg_(i-1) = dg_i + do_(i-1) . o_(i-1) - dv_(i-1) . v_(i-1),
+// started from <dh, S_n> at the block's end and again from <dS, S> at its middle (every
+// rounding of a state between start and use stays in the sum), with do . o = q . dq and
+// dv . v = beta dbeta - k . (second part of dk), summed in 64 bits.
+//
+// Layout: 16 lanes of a DPP row share a column's rows (d_k / 16 consecutive rows each), so a
+// column sum over rows is four DPP adds; the four DPP rows hold different columns.  Row sums
+// over columns go over the DPP rows by permlane swaps and over waves through LDS, in a fixed
+// order (deterministic, no atomics; the v-heads of a q/k head are added in turn).
+//
+// What bounds it: the instructions of the two serial walks, one wave in order (0.11 us per
+// step forwards, 0.15 us backwards), and in the block kernels three walks of a block each.
+// Measured at 1 x 256 + 256 tokens, 2 heads, d = 64, L = 16 in fp32: states 28 us, noisy
+// 31 us, reverse 38 us, clean 29 us; the one-wave walk of bwd_generic.hip, whose steps waited
+// for loads and for two butterflies over the columns each, 4.04 ms.  The walks' 4-column
+// tiles and per-chunk row pointers: 41 + 53 us with a 64-bit row product per position.
+#include "bwd.hpp"
+#include "common.hpp"
+#include "kernels.hpp"
+#include "ut.hpp"
+
+namespace bdgdn {
+
+namespace {
+
+constexpr int kSpan = 4;        // positions per row-sum exchange between the waves of a block
+constexpr int kMaxL = 64;
+constexpr int kStepStreams = 5; // the clean stream and up to four noisy views
+
+struct StepStream {
+    const void *q, *k, *v;
+    const float *g, *beta;
+    const void *dout;
+    float *dq, *dk, *dv, *dg, *db;
+};
+
+struct StepArgs {
+    StepStream st[kStepStreams];   // 0 clean, 1 .. n_views noisy
+    int n_views;
+    const int32_t *cu;             // packed documents, or null
+    int n_seq;
+    const float *h0, *dht;
+    float *dh0;
+    float *seeds;                  // [block][h_v][d_v][d_k]: the clean state before each block
+    float *dh;                     // same: the seed's gradient, then the gradient at the block's end
+    int T, L, nblk, h_qk, h_v;
+    float scale;
+};
+
+// NR consecutive elements, loaded as a whole.
+template <typename T, int NR> struct alignas(sizeof(T) * NR > 16 ? 16 : sizeof(T) * NR) Vec {
+    T v[NR];
+};
+template <typename T, int NR> __device__ __forceinline__ Vec<T, NR> ldv(const T *p)
+{
+    return *reinterpret_cast<const Vec<T, NR> *>(p);
+}
+
+// x summed over the 16 lanes of each DPP row, in every lane
+__device__ __forceinline__ float row16_sum(float x)
+{
+    x += ut::dpp<0x128>(x);   // row_ror:8
+    x += ut::dpp<0x124>(x);
+    x += ut::dpp<0x122>(x);
+    x += ut::dpp<0x121>(x);
+    return x;
+}
+// a in the lower and b in the upper 32 lanes, each summed with the other half's value
+__device__ __forceinline__ float swap32_sum(float a, float b)
+{
+    const auto r = __builtin_amdgcn_permlane32_swap(__builtin_bit_cast(unsigned, a), __builtin_bit_cast(unsigned, b),
+                                                    false, false);
+    return __builtin_bit_cast(float, (unsigned)r[0]) + __builtin_bit_cast(float, (unsigned)r[1]);
+}
+// the same between neighbouring DPP rows: a in the even rows, b in the odd rows
+__device__ __forceinline__ float swap16_sum(float a, float b)
+{
+    const auto r = __builtin_amdgcn_permlane16_swap(__builtin_bit_cast(unsigned, a), __builtin_bit_cast(unsigned, b),
+                                                    false, false);
+    return __builtin_bit_cast(float, (unsigned)r[0]) + __builtin_bit_cast(float, (unsigned)r[1]);
+}
+__device__ __forceinline__ float rows4_sum(float x)
+{
+    x = swap32_sum(x, x);
+    return swap16_sum(x, x);
+}
+// x[m] (m < NR) summed over the four DPP rows; lane (cg, rl) ends with the sums of rows
+// cg NR / 4 .. cg NR / 4 + NR / 4 - 1 of its NR rows in x[0 .. NR / 4 - 1]
+template <int NR> __device__ __forceinline__ void rows4_scatter(float (&x)[NR])
+{
+#pragma unroll
+    for (int m = 0; m < NR / 2; ++m) x[m] = swap32_sum(x[m], x[m + NR / 2]);
+#pragma unroll
+    for (int m = 0; m < NR / 4; ++m) x[m] = swap16_sum(x[m], x[m + NR / 4]);
+}
+
+// A chain's first row, length and the workspace unit of its first block.
+__device__ __forceinline__ void chain_span(const StepArgs &a, int seq, long &base, long &len, long &blk0)
+{
+    if (a.cu) {
+        base = a.cu[seq];
+        len = (long)a.cu[seq + 1] - base;
+        blk0 = base / a.L;   // documents start on block boundaries
+    } else {
+        base = (long)seq * a.T;
+        len = a.T;
+        blk0 = (long)seq * a.nblk;
+    }
+}
+
+// The (chain, 4-column tile) of a one-wave workgroup: the tiles of a chain on one XCD
+// (workgroups are dealt to the 8 XCDs in turn), so that they share its k and q rows in L2.
+template <int DV> __device__ __forceinline__ bool walk_unit(const StepArgs &a, int &seq, int &h, int &tile)
+{
+    constexpr int NT = DV / 4;
+    const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
+    const int chain = slot / NT * 8 + xcd;
+    tile = slot % NT;
+    seq = chain / a.h_v;
+    h = chain % a.h_v;
+    return chain < a.n_seq * a.h_v;
+}
+template <int DV> unsigned walk_grid(const StepArgs &a)
+{
+    const long chains = (long)a.n_seq * a.h_v;
+    return (unsigned)((chains + 7) / 8 * 8 * (DV / 4));
+}
+
+}  // namespace
+
+// Phase 1: the clean state before every block of each chain, column-major.  Bound by the
+// instructions of one step after another (one wave per 4 columns, P positions of loads in
+// flight behind the P being walked).
+template <typename In, int DK, int DV>
+__global__ void __launch_bounds__(64) bdgdn_bwd_steps_states_kernel(StepArgs a)
+{
+    constexpr int NR = DK / 16, P = 8;
+    int seq, h, tile;
+    if (!walk_unit<DV>(a, seq, h, tile)) return;
+    const int lane = threadIdx.x, rl = lane & 15, col = 4 * tile + (lane >> 4), hq = h / (a.h_v / a.h_qk);
+    long base, len, blk0;
+    chain_span(a, seq, base, len, blk0);
+    float S[NR];
+#pragma unroll
+    for (int m = 0; m < NR; ++m)
+        S[m] = a.h0 ? a.h0[((long)(seq * a.h_v + h) * DK + rl * NR + m) * DV + col] : 0.f;
+    if (len <= 0) return;
+    // uniform row pointers and one lane offset each
+    const In *kp = static_cast<const In *>(a.st[0].k) + (base * a.h_qk + hq) * DK;
+    const In *vp = static_cast<const In *>(a.st[0].v) + (base * a.h_v + h) * DV;
+    const unsigned ko = rl * NR, vo = col;
+    const long qks = (long)a.h_qk * DK, vs = (long)a.h_v * DV;
+    const float *gp = a.st[0].g + base * a.h_v + h, *bp = a.st[0].beta + base * a.h_v + h;
+    struct Buf {
+        Vec<In, NR> k[P];
+        In v[P];
+    };
+    // the P positions from the running row pointers on (whole chunks without a row index)
+    const In *kc = kp, *vc = vp;
+    auto fetch = [&](Buf &b, long i0) {
+        if (i0 + P <= len) {
+#pragma unroll
+            for (int j = 0; j < P; ++j) {
+                b.k[j] = ldv<In, NR>(kc + j * qks + ko);
+                b.v[j] = (vc + j * vs)[vo];
+            }
+            kc += P * qks;
+            vc += P * vs;
+        } else {
+#pragma unroll
+            for (int j = 0; j < P; ++j) {
+                const long i = i0 + j < len ? i0 + j : len - 1;
+                b.k[j] = ldv<In, NR>(kp + i * qks + ko);
+                b.v[j] = (vp + i * vs)[vo];
+            }
+        }
+    };
+    auto gate_row = [&](long i0) { return (i0 + lane < len ? i0 + lane : len - 1) * a.h_v; };
+    // gates of 64 positions, one a lane, the next 64 in flight
+    float ng = gp[gate_row(0)], nb = bp[gate_row(0)], al = 0.f, be = 0.f;
+    int left = 0;      // positions to the next block start
+    float *seed = a.seeds + ((blk0 * a.h_v + h) * DV + col) * (long)DK + rl * NR;
+    auto walk = [&](const Buf &b, long i0) {
+        if ((i0 & 63) == 0) {
+            al = expf(ng);
+            be = nb;
+            ng = gp[gate_row(i0 + 64)];
+            nb = bp[gate_row(i0 + 64)];
+        }
+#pragma unroll
+        for (int j = 0; j < P; ++j) {
+            if (i0 + j >= len) break;
+            if (left == 0) {
+#pragma unroll
+                for (int m = 0; m < NR; m += 4) st4(seed + m, S[m], S[m + 1], S[m + 2], S[m + 3]);
+                seed += (long)a.h_v * DV * DK;
+                left = a.L;
+            }
+            --left;
+            const int at = (int)(i0 & 63) + j;
+            const float alpha = ut::lane_value(al, at), beta = ut::lane_value(be, at);
+            float k[NR], x = 0.f;
+#pragma unroll
+            for (int m = 0; m < NR; ++m) {
+                k[m] = to_f(b.k[j].v[m]);
+                x = fmaf(k[m], S[m], x);
+            }
+            const float bu = beta * (to_f(b.v[j]) - alpha * row16_sum(x));
+#pragma unroll
+            for (int m = 0; m < NR; ++m) S[m] = fmaf(k[m], bu, alpha * S[m]);
+        }
+    };
+    Buf b0, b1;
+    fetch(b0, 0);
+    for (long i = 0; i < len; i += 2 * P) {
+        fetch(b1, i + P);
+        walk(b0, i);
+        if (i + P >= len) break;
+        fetch(b0, i + 2 * P);
+        walk(b1, i + P);
+    }
+}
+
+// Phase 3: the reverse walk of the clean state gradient: dh at every block's end over the
+// block's seed gradient (read before), the seed gradient added at the block's start; dh0.
+template <typename In, typename Out, int DK, int DV>
+__global__ void __launch_bounds__(64) bdgdn_bwd_steps_reverse_kernel(StepArgs a)
+{
+    constexpr int NR = DK / 16, P = 8;
+    int seq, h, tile;
+    if (!walk_unit<DV>(a, seq, h, tile)) return;
+    const int lane = threadIdx.x, rl = lane & 15, col = 4 * tile + (lane >> 4), hq = h / (a.h_v / a.h_qk);
+    long base, len, blk0;
+    chain_span(a, seq, base, len, blk0);
+    float dS[NR];
+    const long edge = ((long)(seq * a.h_v + h) * DK + rl * NR) * DV + col;   // of h0, dht, dh0
+#pragma unroll
+    for (int m = 0; m < NR; ++m) dS[m] = a.dht ? a.dht[edge + (long)m * DV] : 0.f;
+    if (len > 0) {
+        const In *kp = static_cast<const In *>(a.st[0].k) + (base * a.h_qk + hq) * DK;
+        const In *qp = static_cast<const In *>(a.st[0].q) + (base * a.h_qk + hq) * DK;
+        const Out *dp = static_cast<const Out *>(a.st[0].dout) + (base * a.h_v + h) * DV;
+        const unsigned ko = rl * NR, vo = col;
+        const long qks = (long)a.h_qk * DK, vs = (long)a.h_v * DV;
+        const float *gp = a.st[0].g + base * a.h_v + h, *bp = a.st[0].beta + base * a.h_v + h;
+        struct Buf {
+            Vec<In, NR> k[P], q[P];
+            Out d[P];
+        };
+        // position j of the walk is row len - 1 - j
+        const In *kc = kp + (len - 1) * qks, *qc = qp + (len - 1) * qks;
+        const Out *dc = dp + (len - 1) * vs;
+        auto fetch = [&](Buf &b, long j0) {
+            if (j0 + P <= len) {
+#pragma unroll
+                for (int j = 0; j < P; ++j) {
+                    b.k[j] = ldv<In, NR>(kc - j * qks + ko);
+                    b.q[j] = ldv<In, NR>(qc - j * qks + ko);
+                    b.d[j] = (dc - j * vs)[vo];
+                }
+                kc -= P * qks;
+                qc -= P * qks;
+                dc -= P * vs;
+                return;
+            }
+#pragma unroll
+            for (int j = 0; j < P; ++j) {
+                const long i = len - 1 - j0 - j > 0 ? len - 1 - j0 - j : 0;
+                b.k[j] = ldv<In, NR>(kp + i * qks + ko);
+                b.q[j] = ldv<In, NR>(qp + i * qks + ko);
+                b.d[j] = (dp + i * vs)[vo];
+            }
+        };
+        auto gate_row = [&](long j0) { return (len - 1 - j0 - lane > 0 ? len - 1 - j0 - lane : 0) * a.h_v; };
+        float ng = gp[gate_row(0)], nb = bp[gate_row(0)], al = 0.f, be = 0.f;
+        const long unit = (long)a.h_v * DV * DK;
+        const long nblk = (len + a.L - 1) / a.L;
+        float *slot = a.dh + (((blk0 + nblk - 1) * a.h_v + h) * DV + col) * (long)DK + rl * NR;   // the last block's
+        int left = (int)(len - (nblk - 1) * a.L);   // positions of the current block still to walk
+        float cur[NR];   // the seed gradient of the current block
+        bool ends = true;   // the next position is its block's last
+        auto walk = [&](const Buf &b, long j0) {
+            if ((j0 & 63) == 0) {
+                al = expf(ng);
+                be = nb;
+                ng = gp[gate_row(j0 + 64)];
+                nb = bp[gate_row(j0 + 64)];
+            }
+#pragma unroll
+            for (int j = 0; j < P; ++j) {
+                if (j0 + j >= len) break;
+                if (ends) {   // the seed gradient out of the block's slot, dh into it
+#pragma unroll
+                    for (int m = 0; m < NR; m += 4) {
+                        const f32x4 y = *reinterpret_cast<const f32x4 *>(slot + m);
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) cur[m + e] = y[e];
+                    }
+#pragma unroll
+                    for (int m = 0; m < NR; m += 4) st4(slot + m, dS[m], dS[m + 1], dS[m + 2], dS[m + 3]);
+                    ends = false;
+                }
+                const int at = (int)(j0 & 63) + j;
+                const float alpha = ut::lane_value(al, at), beta = ut::lane_value(be, at);
+                const float d = a.scale * to_f(b.d[j]);
+                float k[NR], w = 0.f;
+#pragma unroll
+                for (int m = 0; m < NR; ++m) {
+                    k[m] = to_f(b.k[j].v[m]);
+                    dS[m] = fmaf(to_f(b.q[j].v[m]), d, dS[m]);
+                    w = fmaf(k[m], dS[m], w);
+                }
+                const float bw = beta * row16_sum(w);
+#pragma unroll
+                for (int m = 0; m < NR; ++m) dS[m] = alpha * fmaf(-k[m], bw, dS[m]);
+                if (--left == 0) {   // the block's start: the noisy seeds' gradient joins
+#pragma unroll
+                    for (int m = 0; m < NR; ++m) dS[m] += cur[m];
+                    slot -= unit;
+                    left = a.L;
+                    ends = true;
+                }
+            }
+        };
+        Buf b0, b1;
+        fetch(b0, 0);
+        for (long j = 0; j < len; j += 2 * P) {
+            fetch(b1, j + P);
+            walk(b0, j);
+            if (j + P >= len) break;
+            fetch(b0, j + 2 * P);
+            walk(b1, j + P);
+        }
+    }
+    if (a.dh0) {
+#pragma unroll
+        for (int m = 0; m < NR; ++m) a.dh0[edge + (long)m * DV] = dS[m];
+    }
+}
+
+namespace {
+
+// LDS of a block kernel with W = DV / 16 waves: the block's rows, its per-column u and w, the
+// row-sum exchange and the per-position sums over columns (one entry per wave).
+template <typename In, typename Out, int DK, int DV> struct BlockLds {
+    static constexpr int W = DV / 16;
+    In *q, *k;       // [L][DK]
+    Out *d;          // [L][DV]
+    float *u, *w;    // [L][DV]: u holds v until u replaces it
+    float *red;      // [W][kSpan][DK]
+    float *pa, *pb, *pc;   // [L][W]: q . dq, w . u, k . (second part of dk)
+    float *al, *be;  // [kMaxL]
+    float *tot, *mid;   // [W]: <dh, S_n> and <dS, S> at the block's middle
+    static size_t bytes(int L)
+    {
+        return (size_t)L * (2 * DK * sizeof(In) + DV * sizeof(Out) + 2 * DV * 4 + 3 * W * 4) + W * kSpan * DK * 4 +
+               2 * kMaxL * 4 + 2 * W * 4;
+    }
+    __device__ BlockLds(unsigned char *p, int L)
+    {
+        u = reinterpret_cast<float *>(p);
+        w = u + L * DV;
+        red = w + L * DV;
+        pa = red + W * kSpan * DK;
+        pb = pa + L * W;
+        pc = pb + L * W;
+        al = pc + L * W;
+        be = al + kMaxL;
+        tot = be + kMaxL;
+        mid = tot + W;
+        q = reinterpret_cast<In *>(mid + W);
+        k = q + L * DK;
+        d = reinterpret_cast<Out *>(k + L * DK);
+    }
+};
+
+template <typename In, typename Out, int DK, int DV> struct Block {
+    static constexpr int NR = DK / 16, W = DV / 16, NT = 64 * W;
+    typedef BlockLds<In, Out, DK, DV> Lds;
+    const StepArgs &a;
+    Lds s;
+    int tid, lane, wave, rl, col;   // col: this lane's first of 4 columns
+    int n;                          // positions of the block
+    float S[NR][4];
+
+    __device__ Block(const StepArgs &a_, unsigned char *smem) : a(a_), s(smem, a_.L)
+    {
+        tid = threadIdx.x;
+        lane = tid & 63;
+        wave = tid >> 6;
+        rl = lane & 15;
+        col = 16 * wave + 4 * (lane >> 4);
+    }
+    // rows of [n][D] elements into LDS, 16 bytes a thread
+    template <typename T, int D> __device__ __forceinline__ void stage(T *dst, const T *src, long stride) const
+    {
+        constexpr int E = 16 / sizeof(T);
+        for (int e = tid; e < n * (D / E); e += NT) {
+            const int r = e / (D / E), c = e % (D / E) * E;
+            *reinterpret_cast<Vec<T, E> *>(dst + r * D + c) = ldv<T, E>(src + r * stride + c);
+        }
+    }
+    __device__ __forceinline__ void load_state(float (&x)[NR][4], const float *p) const   // column-major
+    {
+#pragma unroll
+        for (int c = 0; c < 4; ++c)
+#pragma unroll
+            for (int m = 0; m < NR; m += 4) {
+                const f32x4 y = *reinterpret_cast<const f32x4 *>(p + (long)(col + c) * DK + rl * NR + m);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) x[m + e][c] = y[e];
+            }
+    }
+    __device__ __forceinline__ void load_k(float (&x)[NR], const In *rows, int i) const
+    {
+        const Vec<In, NR> y = ldv<In, NR>(rows + i * DK + rl * NR);
+#pragma unroll
+        for (int m = 0; m < NR; ++m) x[m] = to_f(y.v[m]);
+    }
+    template <typename T> __device__ __forceinline__ void load_c(float (&x)[4], const T *rows, int i) const
+    {
+        const Vec<T, 4> y = ldv<T, 4>(rows + i * DV + col);
+#pragma unroll
+        for (int c = 0; c < 4; ++c) x[c] = to_f(y.v[c]);
+    }
+    // this wave's sums over its columns of the row vector x of position i0 + slot
+    __device__ __forceinline__ void put_rows(float (&x)[NR], int slot)
+    {
+        rows4_scatter<NR>(x);
+        float *p = s.red + (wave * kSpan + slot) * DK + rl * NR + (lane >> 4) * (NR / 4);
+#pragma unroll
+        for (int m = 0; m < NR / 4; ++m) p[m] = x[m];
+    }
+    // the waves' row sums of positions i0 .. i0 + cnt - 1 to dst (rows of stride ld): stored,
+    // or added to what this same thread stored before
+    __device__ __forceinline__ void flush(float *dst, long ld, int i0, int cnt, bool add)
+    {
+        __syncthreads();
+        for (int e = tid; e < cnt * DK; e += NT) {
+            const int sl = e / DK, r = e % DK;
+            float x = 0.f;
+#pragma unroll
+            for (int v = 0; v < W; ++v) x += s.red[(v * kSpan + sl) * DK + r];
+            float *p = dst + (long)(i0 + sl) * ld + r;
+            *p = add ? *p + x : x;
+        }
+        __syncthreads();
+    }
+
+    __device__ __forceinline__ void store_state(float *p, const float (&x)[NR][4]) const
+    {
+#pragma unroll
+        for (int c = 0; c < 4; ++c)
+#pragma unroll
+            for (int m = 0; m < NR; m += 4)
+                st4(p + (long)(col + c) * DK + rl * NR + m, x[m][c], x[m + 1][c], x[m + 2][c], x[m + 3][c]);
+    }
+    // <x, y> over this wave's columns, in every lane
+    __device__ __forceinline__ float inner(const float (&x)[NR][4], const float (&y)[NR][4]) const
+    {
+        float e = 0.f;
+#pragma unroll
+        for (int m = 0; m < NR; ++m)
+#pragma unroll
+            for (int c = 0; c < 4; ++c) e = fmaf(x[m][c], y[m][c], e);
+        return rows4_sum(row16_sum(e));
+    }
+
+    // The block of stream st (clean, or a noisy view) for v-head h: rows from row p0; seed: the
+    // state at its start; spare: a state's room (the block's slot of dh, free meanwhile) for the
+    // state at its middle; dS: clean, the gradient at its end (in); noisy, the gradient of its
+    // seed (out).  add: dq, dk add to an earlier v-head's.
+    template <bool CLEAN>
+    __device__ void run(const StepStream &st, long p0, int h, int hq, const float *seed, float *spare,
+                        float (&dS)[NR][4], bool add)
+    {
+        const int half = n / 2 / kSpan * kSpan;   // 0: a short block, no restart
+        const long qks = (long)a.h_qk * DK, vs = (long)a.h_v * DV;
+        const long qo = (p0 * a.h_qk + hq) * DK, vo = (p0 * a.h_v + h) * DV, go = p0 * a.h_v + h;
+        stage<In, DK>(s.q, static_cast<const In *>(st.q) + qo, qks);
+        stage<In, DK>(s.k, static_cast<const In *>(st.k) + qo, qks);
+        stage<Out, DV>(s.d, static_cast<const Out *>(st.dout) + vo, vs);
+        for (int e = tid; e < n * (DV / 4); e += NT) {   // v as fp32
+            const int r = e / (DV / 4), c = e % (DV / 4) * 4;
+            const Vec<In, 4> x = ldv<In, 4>(static_cast<const In *>(st.v) + vo + r * vs + c);
+            st4(s.u + r * DV + c, to_f(x.v[0]), to_f(x.v[1]), to_f(x.v[2]), to_f(x.v[3]));
+        }
+        if (tid < n) {
+            s.al[tid] = expf(st.g[go + (long)tid * a.h_v]);
+            s.be[tid] = st.beta[go + (long)tid * a.h_v];
+        }
+        load_state(S, seed);
+        __syncthreads();
+        float *dq = st.dq + qo, *dk = st.dk + qo;
+        // forwards: u over v; clean: dq
+        for (int i0 = 0; i0 < n; i0 += kSpan) {
+            const int cnt = n - i0 < kSpan ? n - i0 : kSpan;
+            if (i0 > 0 && i0 == half) store_state(spare, S);
+            for (int j = 0; j < cnt; ++j) {
+                const int i = i0 + j;
+                float k[NR], u[4];
+                load_k(k, s.k, i);
+                load_c(u, s.u, i);
+                const float alpha = s.al[i], beta = s.be[i];
+#pragma unroll
+                for (int c = 0; c < 4; ++c) {
+                    float x = 0.f;
+#pragma unroll
+                    for (int m = 0; m < NR; ++m) x = fmaf(k[m], S[m][c], x);
+                    u[c] -= alpha * row16_sum(x);
+                    const float bu = beta * u[c];
+#pragma unroll
+                    for (int m = 0; m < NR; ++m) S[m][c] = fmaf(alpha, S[m][c], k[m] * bu);
+                }
+                if (rl == 0) st4(s.u + i * DV + col, u[0], u[1], u[2], u[3]);
+                if constexpr (CLEAN) read_out(i, j);
+            }
+            if constexpr (CLEAN) flush(dq, qks, i0, cnt, add);
+        }
+        if constexpr (CLEAN) {
+            const float e = inner(dS, S);   // <dh, S_n>
+            if (lane == 0) s.tot[wave] = e;
+        } else {
+            // every position reads the end state: dq_i = s S~ do_i, dS~ = s sum q_i do_i^T
+#pragma unroll
+            for (int m = 0; m < NR; ++m)
+#pragma unroll
+                for (int c = 0; c < 4; ++c) dS[m][c] = 0.f;
+            for (int i0 = 0; i0 < n; i0 += kSpan) {
+                const int cnt = n - i0 < kSpan ? n - i0 : kSpan;
+                for (int j = 0; j < cnt; ++j) {
+                    read_out(i0 + j, j);
+                    add_outer(dS, i0 + j);
+                }
+                flush(dq, qks, i0, cnt, add);
+            }
+        }
+        // backwards: w, dbeta, the first part of dk
+        for (int i0 = (n - 1) / kSpan * kSpan; i0 >= 0; i0 -= kSpan) {
+            const int cnt = n - i0 < kSpan ? n - i0 : kSpan;
+            for (int j = cnt - 1; j >= 0; --j) {
+                const int i = i0 + j;
+                if constexpr (CLEAN) add_outer(dS, i);
+                float k[NR], u[4], w[4], e[NR], b = 0.f;
+                load_k(k, s.k, i);
+                load_c(u, s.u, i);
+                const float alpha = s.al[i], beta = s.be[i];
+#pragma unroll
+                for (int m = 0; m < NR; ++m) e[m] = 0.f;
+#pragma unroll
+                for (int c = 0; c < 4; ++c) {
+                    float x = 0.f;
+#pragma unroll
+                    for (int m = 0; m < NR; ++m) {
+                        x = fmaf(k[m], dS[m][c], x);
+                        e[m] = fmaf(dS[m][c], u[c], e[m]);
+                    }
+                    w[c] = row16_sum(x);
+                    b = fmaf(w[c], u[c], b);
+                    const float bw = beta * w[c];
+#pragma unroll
+                    for (int m = 0; m < NR; ++m) dS[m][c] = alpha * fmaf(-k[m], bw, dS[m][c]);
+                }
+                b = rows4_sum(b);
+#pragma unroll
+                for (int m = 0; m < NR; ++m) e[m] *= beta;
+                if (rl == 0) st4(s.w + i * DV + col, w[0], w[1], w[2], w[3]);
+                if (lane == 0) s.pb[i * W + wave] = b;
+                put_rows(e, j);
+            }
+            flush(dk, qks, i0, cnt, add);
+            if (i0 > 0 && i0 == half) {
+                load_state(S, spare);   // written by this lane
+                const float e = inner(dS, S);
+                if (lane == 0) s.mid[wave] = e;
+            }
+        }
+        // forwards again: the second part of dk, -alpha beta S w
+        load_state(S, seed);
+        for (int i0 = 0; i0 < n; i0 += kSpan) {
+            const int cnt = n - i0 < kSpan ? n - i0 : kSpan;
+            for (int j = 0; j < cnt; ++j) {
+                const int i = i0 + j;
+                float k[NR], u[4], w[4], e[NR], b = 0.f;
+                load_k(k, s.k, i);
+                load_c(u, s.u, i);
+                load_c(w, s.w, i);
+                const float alpha = s.al[i], beta = s.be[i], f = -alpha * beta;
+#pragma unroll
+                for (int m = 0; m < NR; ++m) {
+                    float x = 0.f;
+#pragma unroll
+                    for (int c = 0; c < 4; ++c) {
+                        x = fmaf(S[m][c], w[c], x);
+                        S[m][c] = fmaf(alpha, S[m][c], k[m] * (beta * u[c]));
+                    }
+                    e[m] = f * x;
+                    b = fmaf(k[m], e[m], b);
+                }
+                b = rows4_sum(row16_sum(b));
+                if (lane == 0) s.pc[i * W + wave] = b;
+                put_rows(e, j);
+            }
+            flush(dk, qks, i0, cnt, true);
+        }
+        // dv = beta w; dbeta; dg by the reverse sum of q . dq (clean) - dv . v
+        for (int e = tid; e < n * (DV / 4); e += NT) {
+            const int r = e / (DV / 4), c = e % (DV / 4) * 4;
+            const f32x4 x = *reinterpret_cast<const f32x4 *>(s.w + r * DV + c);
+            const float b = s.be[r];
+            st4(st.dv + vo + r * vs + c, b * x[0], b * x[1], b * x[2], b * x[3]);
+        }
+        if (wave == 0) {
+            // the gate gradient is a difference of sums over the block: taken in 64 bits
+            float b = 0.f;
+            double qa = 0., e = 0., end = 0.;
+            if (lane < n) {
+#pragma unroll
+                for (int v = 0; v < W; ++v) {
+                    qa += s.pa[lane * W + v];
+                    b += s.pb[lane * W + v];
+                    e += s.pc[lane * W + v];
+                }
+            }
+            if constexpr (CLEAN) {
+#pragma unroll
+                for (int v = 0; v < W; ++v) end += s.tot[v];
+            } else {
+                end = qa;
+#pragma unroll
+                for (int o = 1; o < 64; o <<= 1) end += __shfl_xor(end, o);
+                qa = 0.;
+            }
+            double x = lane < n ? qa - (double)s.be[lane] * b + e : 0., start = 0.;
+            if (half > 0) {
+#pragma unroll
+                for (int v = 0; v < W; ++v) start += s.mid[v];
+            }
+#pragma unroll
+            for (int o = 1; o < 64; o <<= 1) {
+                const double y = __shfl_down(x, o);
+                if (lane + o < 64) x += y;
+            }
+            const double later = __shfl(x, half);   // the terms from the middle on
+            if (lane < half)
+                x += start - later;
+            else
+                x += end;
+            if (lane < n) {
+                st.db[go + (long)lane * a.h_v] = b;
+                st.dg[go + (long)lane * a.h_v] = (float)x;
+            }
+        }
+        __syncthreads();   // LDS is free for the next v-head or view
+    }
+    // dq of position i from the state in S, into exchange slot j; q . dq into pa
+    __device__ __forceinline__ void read_out(int i, int j)
+    {
+        float q[NR], d[4], p[NR], b = 0.f;
+        load_k(q, s.q, i);
+        load_c(d, s.d, i);
+#pragma unroll
+        for (int m = 0; m < NR; ++m) {
+            float x = 0.f;
+#pragma unroll
+            for (int c = 0; c < 4; ++c) x = fmaf(S[m][c], d[c], x);
+            p[m] = a.scale * x;
+            b = fmaf(q[m], p[m], b);
+        }
+        b = rows4_sum(row16_sum(b));
+        if (lane == 0) s.pa[i * W + wave] = b;
+        put_rows(p, j);
+    }
+    __device__ __forceinline__ void add_outer(float (&dS)[NR][4], int i)
+    {
+        float q[NR], d[4];
+        load_k(q, s.q, i);
+        load_c(d, s.d, i);
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+            const float x = a.scale * d[c];
+#pragma unroll
+            for (int m = 0; m < NR; ++m) dS[m][c] = fmaf(q[m], x, dS[m][c]);
+        }
+    }
+};
+
+// First row and positions of global block blk.
+__device__ __forceinline__ void block_span(const StepArgs &a, long blk, long &p0, int &n)
+{
+    long rem;
+    if (a.cu) {
+        p0 = blk * a.L;
+        int lo = 0, hi = a.n_seq;   // the last document with cu[d] <= p0
+        while (hi - lo > 1) {
+            const int mid = (lo + hi) >> 1;
+            if (a.cu[mid] <= p0)
+                lo = mid;
+            else
+                hi = mid;
+        }
+        rem = a.cu[lo + 1] - p0;
+    } else {
+        const long s = blk / a.nblk, b = blk % a.nblk;
+        p0 = s * a.T + b * a.L;
+        rem = a.T - b * a.L;
+    }
+    n = (int)(rem < a.L ? rem : a.L);
+}
+
+}  // namespace
+
+// Phases 2 and 4: one workgroup per (block, q/k head) runs the v-heads in turn, and the
+// noisy views of each; phase 2 leaves the sum of the views' seed gradients in dh, phase 4
+// reads the gradient at the block's end there.
+template <typename In, typename Out, int DK, int DV, bool CLEAN>
+__global__ void __launch_bounds__(4 * DV) bdgdn_bwd_steps_block_kernel(StepArgs a)
+{
+    extern __shared__ __align__(16) unsigned char smem_raw[];
+    typedef Block<In, Out, DK, DV> B;
+    B b(a, smem_raw);
+    const long blk = blockIdx.x / a.h_qk;
+    const int hq = blockIdx.x % a.h_qk, r = a.h_v / a.h_qk;
+    long p0;
+    block_span(a, blk, p0, b.n);
+    if (b.n <= 0) return;
+    for (int vi = 0; vi < r; ++vi) {
+        const int h = hq * r + vi;
+        const long so = (blk * a.h_v + h) * (long)DV * DK;
+        float dS[B::NR][4];
+        if constexpr (CLEAN) {
+            b.load_state(dS, a.dh + so);
+            b.template run<true>(a.st[0], p0, h, hq, a.seeds + so, a.dh + so, dS, vi > 0);
+        } else {
+            float acc[B::NR][4] = {};
+            for (int v = 1; v <= a.n_views; ++v) {
+                b.template run<false>(a.st[v], p0, h, hq, a.seeds + so, a.dh + so, dS, vi > 0);
+#pragma unroll
+                for (int m = 0; m < B::NR; ++m)
+#pragma unroll
+                    for (int c = 0; c < 4; ++c) acc[m][c] += dS[m][c];
+            }
+            b.store_state(a.dh + so, acc);
+        }
+    }
+}
+
+namespace {
+
+template <typename In, typename Out, int DK, int DV> hipError_t launch(const StepArgs &a, long blocks, hipStream_t s)
+{
+    const int lds = (int)BlockLds<In, Out, DK, DV>::bytes(a.L);
+    auto ks = bdgdn_bwd_steps_states_kernel<In, DK, DV>;
+    auto kr = bdgdn_bwd_steps_reverse_kernel<In, Out, DK, DV>;
+    auto kn = bdgdn_bwd_steps_block_kernel<In, Out, DK, DV, false>;
+    auto kc = bdgdn_bwd_steps_block_kernel<In, Out, DK, DV, true>;
+    for (const void *f : {reinterpret_cast<const void *>(kn), reinterpret_cast<const void *>(kc)}) {
+        const hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+        if (e != hipSuccess) return e;
+    }
+    const dim3 walk(walk_grid<DV>(a)), units((unsigned)(blocks * a.h_qk)), nt(4 * DV);
+    hipError_t e;
+    hipLaunchKernelGGL(ks, walk, dim3(64), 0, s, a);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
+    hipLaunchKernelGGL(kn, units, nt, lds, s, a);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
+    hipLaunchKernelGGL(kr, walk, dim3(64), 0, s, a);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
+    hipLaunchKernelGGL(kc, units, nt, lds, s, a);
+    return hipGetLastError();
+}
+
+size_t up256(size_t x) { return (x + 255) & ~(size_t)255; }
+
+}  // namespace
+
+size_t bwd_steps_workspace(long total_blocks, int h_v, int dk, int dv)
+{
+    const size_t states = (size_t)total_blocks * h_v * dk * dv * sizeof(float);
+    const size_t need = 2 * up256(states);
+    return need <= kStepsMaxBytes ? need : 0;
+}
+
+// The line between this schedule and the serial walk is workspace alone: at every size
+// measured this one is faster (7 x at 1 x 48 positions in blocks of 4, 27 x at 1 x 256 in
+// blocks of 16, 38 x at 1 x 371 in blocks of 8), so it runs whenever the caller gives it its
+// two states per (block, v-head).
+hipError_t launch_bwd_steps(bool f32_in, bool f32_out, const GenBwdCall &c, hipStream_t s)
+{
+    StepArgs a = {};
+    a.st[0] = StepStream{c.q, c.k, c.v, c.g, c.beta, c.dout, c.dq, c.dk, c.dv, c.dg, c.db};
+    a.st[1] = StepStream{c.qn, c.kn, c.vn, c.gn, c.betan, c.doutn, c.dqn, c.dkn, c.dvn, c.dgn, c.dbn};
+    a.n_views = 1 + c.n_more;
+    if (!bwd_generic_supported(f32_in, c.d_k, c.d_v, c.L, a.n_views)) return hipErrorInvalidValue;
+    for (int i = 0; i < c.n_more; ++i) {
+        const BwdView &w = c.more[i];
+        a.st[2 + i] = StepStream{w.q, w.k, w.v, w.g, w.beta, w.dout, w.dq, w.dk, w.dv, w.dg, w.db};
+    }
+    a.cu = c.cu;
+    a.n_seq = c.n_seq;
+    a.h0 = c.h0; a.dht = c.dht; a.dh0 = c.dh0;
+    const size_t states = (size_t)c.total_blocks * c.h_v * c.d_k * c.d_v * sizeof(float);
+    a.seeds = static_cast<float *>(c.workspace);
+    a.dh = reinterpret_cast<float *>(static_cast<unsigned char *>(c.workspace) + up256(states));
+    a.T = c.T; a.L = c.L; a.nblk = (c.T + c.L - 1) / c.L;
+    a.h_qk = c.h_qk; a.h_v = c.h_v;
+    a.scale = c.scale;
+#define BDGDN_DIMS(IN, OUT)                                                                     \
+    {                                                                                           \
+        if (c.d_k == 64)                                                                        \
+            return c.d_v == 64 ? launch<IN, OUT, 64, 64>(a, c.total_blocks, s)                  \
+                               : launch<IN, OUT, 64, 128>(a, c.total_blocks, s);                \
+        return c.d_v == 64 ? launch<IN, OUT, 128, 64>(a, c.total_blocks, s)                     \
+                           : launch<IN, OUT, 128, 128>(a, c.total_blocks, s);                   \
+    }
+    if (f32_in) BDGDN_DIMS(float, float)
+    if (f32_out) BDGDN_DIMS(__bf16, float)
+    BDGDN_DIMS(__bf16, __bf16)
+#undef BDGDN_DIMS
+}
+
+}  // namespace bdgdn
