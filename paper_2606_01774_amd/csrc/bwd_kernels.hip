@@ -333,9 +333,12 @@ enum class Mode { Clean, Noisy, Given };
 // product.  hook1() runs once the arrays R, dDl and dO are dead (after the dR / dQ phase),
 // hook2() two phases later: a persistent caller loads the next unit's clean rows in the one
 // and stages them into those arrays in the other.
-template <Mode MODE, typename Od, typename H1, typename H2>
+// With SMALL (Clean only) the chunk's small noisy blocks have left their shares: xd, of dDelta
+// (this lane's C tiles), and the starting values of dk and dg, to which this pass adds.
+template <Mode MODE, typename Od, bool SMALL = false, typename H1, typename H2>
 __device__ __forceinline__ void block_bwd(Smem &sm, const StreamPtrs &p, const BwdArgs &a, int nvalid, const BlockRows<Od, true> &in,
-                          float (&acc)[8][4], int tid, bool add_qk, const H1 &hook1, const H2 &hook2)
+                          float (&acc)[8][4], int tid, bool add_qk, const H1 &hook1, const H2 &hook2,
+                          const f16x4 *xd = nullptr)
 {
     constexpr bool CLEAN = MODE == Mode::Clean;     // per-position outputs
     constexpr bool READOUT = MODE == Mode::Noisy;   // dS_n from the block-end readout
@@ -497,7 +500,8 @@ __device__ __forceinline__ void block_bwd(Smem &sm, const StreamPtrs &p, const B
             for (int j = 0; j < 4; ++j) {
                 const int r = 16 * tm + 4 * g4 + j, c = c0 + rr;
                 const float Dr = ex(Gn - sm.G[r]);
-                sm.dDl[r * LDH + c] = (_Float16)(s * pd[j] + Dr * kds[j]);
+                const float dd = s * pd[j] + Dr * kds[j];
+                sm.dDl[r * LDH + c] = (_Float16)(SMALL ? dd + (float)xd[tm][j] : dd);
                 const float w = Dr * kds[j] * (float)sm.Dl[r * LDH + c];
                 rowg[tm][j] -= w;
                 dlast += w;
@@ -644,7 +648,7 @@ __device__ __forceinline__ void block_bwd(Smem &sm, const StreamPtrs &p, const B
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
                 const int r = 16 * tm + 4 * g4 + j, col = c0 + rr;
-                if (r < nvalid) put_qk(add_qk, p.dk + (long)r * a.h_qk * DD + col, c[j] * inv);
+                if (r < nvalid) put_qk(SMALL || add_qk, p.dk + (long)r * a.h_qk * DD + col, c[j] * inv);
             }
         }
     }
@@ -672,7 +676,7 @@ __device__ __forceinline__ void block_bwd(Smem &sm, const StreamPtrs &p, const B
             if (lane + o < NP) x += y;
         }
         if (lane < nvalid) {
-            p.dg[(long)lane * a.h_v] = x * inv;
+            put_qk(SMALL, p.dg + (long)lane * a.h_v, x * inv);
             p.db[(long)lane * a.h_v] = sm.dB[lane] * inv;
         }
     }
@@ -1224,8 +1228,9 @@ __global__ void __launch_bounds__(512) bdgdn_bwd_pair_kernel(BwdArgs a)
 }
 
 // Phase 3: every clean block, in parallel, from its seed and the gradient at its end (dh,
-// written by the scan); one workgroup per (block, q/k head).
-template <typename Od>
+// written by the scan); one workgroup per (block, q/k head).  SMALL: with the shares of the
+// chunk's small noisy blocks (block_bwd).
+template <typename Od, bool SMALL>
 __global__ void __launch_bounds__(512) bdgdn_bwd_clean_kernel(BwdArgs a)
 {
     extern __shared__ __align__(16) unsigned char smem_raw[];
@@ -1249,9 +1254,17 @@ __global__ void __launch_bounds__(512) bdgdn_bwd_clean_kernel(BwdArgs a)
         store_tiles(sm.dS, dh, tid);
         float no_acc[8][4] = {};   // the clean stream forms no dS0
         // its first barrier covers S0, dS; its last one the next v-head's stores
-        block_bwd<Mode::Clean, Od>(sm, pc, a, nvalid, in, no_acc, tid, vi > 0, [] {}, [] {});
+        f16x4 xd[2];
+        if constexpr (SMALL) {
+            const f16x4 *x = reinterpret_cast<const f16x4 *>(a.xd + ((size_t)gblk * a.h_v + h) * NP * DD) + tid;
+            xd[0] = x[0];
+            xd[1] = x[8 * 64];
+        }
+        block_bwd<Mode::Clean, Od, SMALL>(sm, pc, a, nvalid, in, no_acc, tid, vi > 0, [] {}, [] {}, xd);
     }
 }
+
+#include "bwd_small.hpp"
 
 // Phase 2: the reverse scan of the clean state gradient over the blocks of a (sequence,
 // v-head) (a chain), one workgroup of NW waves per TC = 8 NW columns (the columns are
@@ -1562,34 +1575,46 @@ hipError_t launch_bwd_range(bool bf16_out, const RangeArgs &r, hipStream_t s)
 
 size_t bwd_block_lds() { return sizeof(Smem); }
 
-// The segment tables: thread k walks the sequences, counting the blocks of each inside
+// The segment tables: wave k scans the sequences, 64 at a time, summing the blocks of each inside
 // segment k (and its noisy blocks of two sub-blocks, the last one possibly half).
 __global__ void __launch_bounds__(64) bdgdn_bwd_seg_plan_kernel(const int32_t *cu, int n_seq, int T, int L,
-                                                                int seg_len, int n_seg, int *seg, int *segp)
+                                                                int seg_len, int *seg, int *segp)
 {
-    const int k = blockIdx.x * 64 + threadIdx.x;
-    if (k >= n_seg) return;
+    const int k = blockIdx.x, lane = threadIdx.x;
     int *o = seg + (long)k * (n_seq + 1), *op = segp + (long)k * (n_seq + 1);
-    int acc = 0, accp = 0;
-    for (int n = 0; n < n_seq; ++n) {
-        o[n] = acc;
-        op[n] = accp;
-        const long len = cu ? (long)cu[n + 1] - cu[n] : T;
-        const long nb = (len + L - 1) / L, rest = nb - (long)k * seg_len;
-        const int cnt = rest <= 0 ? 0 : (rest < seg_len ? (int)rest : seg_len);
-        acc += cnt;
-        accp += (cnt + 1) / 2;
+    int acc = 0, accp = 0;   // of the sequences before n0
+    for (int n0 = 0; n0 <= n_seq; n0 += 64) {
+        const int n = n0 + lane;
+        int cnt = 0;
+        if (n < n_seq) {
+            const long len = cu ? (long)cu[n + 1] - cu[n] : T;
+            const long nb = (len + L - 1) / L, rest = nb - (long)k * seg_len;
+            cnt = rest <= 0 ? 0 : (rest < seg_len ? (int)rest : seg_len);
+        }
+        const int cntp = (cnt + 1) / 2;
+        int x = cnt, xp = cntp;
+#pragma unroll
+        for (int d = 1; d < 64; d <<= 1) {
+            const int y = __shfl_up(x, d), yp = __shfl_up(xp, d);
+            if (lane >= d) {
+                x += y;
+                xp += yp;
+            }
+        }
+        if (n <= n_seq) {
+            o[n] = acc + x - cnt;
+            op[n] = accp + xp - cntp;
+        }
+        acc += __shfl(x, 63);
+        accp += __shfl(xp, 63);
     }
-    o[n_seq] = acc;
-    op[n_seq] = accp;
 }
 
 hipError_t launch_bwd_seg_plan(const int32_t *cu, int n_seq, int T, int L, int seg_len, int n_seg, int *seg,
                                int *segp, hipStream_t s)
 {
     if (n_seg <= 0 || n_seq <= 0 || L <= 0 || seg_len <= 0) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(bdgdn_bwd_seg_plan_kernel, dim3((n_seg + 63) / 64), dim3(64), 0, s, cu, n_seq, T, L, seg_len,
-                       n_seg, seg, segp);
+    hipLaunchKernelGGL(bdgdn_bwd_seg_plan_kernel, dim3(n_seg), dim3(64), 0, s, cu, n_seq, T, L, seg_len, seg, segp);
     return hipGetLastError();
 }
 
@@ -1597,6 +1622,7 @@ hipError_t launch_bwd(bool bf16_out, const BwdArgs &a, const BwdView *more, int 
                       long n_block_units, long n_pair_units, hipStream_t s)
 {
     if (n_more < 0 || (n_more > 0 && !more)) return hipErrorInvalidValue;
+    if (a.nl > 0 && (n_more > 0 || n_pair_units > 0 || a.L != NP || NP % a.nl != 0 || !a.xd)) return hipErrorInvalidValue;
     // one workgroup per (block, q/k head), running its r v-heads in turn (unit_of)
     const int r = a.h_v / a.h_qk;
     const long groups = n_block_units / r, pair_groups = n_pair_units / r;
@@ -1615,15 +1641,22 @@ hipError_t launch_bwd(bool bf16_out, const BwdArgs &a, const BwdView *more, int 
     if (err == hipSuccess) err = hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev);
     if (err != hipSuccess) return err;
     const unsigned pgrid = (unsigned)(groups < n_cu ? groups : (n_cu > 0 ? n_cu : 1));
-    auto run = [&](auto noisy, auto noisy_more, auto pair, auto pair_more, auto clean) {
+    auto run = [&](auto noisy, auto noisy_more, auto pair, auto pair_more, auto small, auto clean, auto clean_small) {
         for (const void *f : {reinterpret_cast<const void *>(noisy), reinterpret_cast<const void *>(noisy_more),
                               reinterpret_cast<const void *>(pair), reinterpret_cast<const void *>(pair_more),
-                              reinterpret_cast<const void *>(clean)}) {
+                              reinterpret_cast<const void *>(clean), reinterpret_cast<const void *>(clean_small)}) {
             const hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)sizeof(Smem));
             if (e != hipSuccess) return e;
         }
-        hipError_t e;
-        if (pair_groups > 0) {   // noisy blocks of two sub-blocks
+        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(small),
+                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)sizeof(SmallSmem));
+        if (e != hipSuccess) return e;
+        if (a.nl > 0) {   // small noisy blocks in clean chunks
+            if (groups > 0) {
+                hipLaunchKernelGGL(small, dim3(pgrid), dim3(512), sizeof(SmallSmem), s, a2);
+                if ((e = hipGetLastError()) != hipSuccess) return e;
+            }
+        } else if (pair_groups > 0) {   // noisy blocks of two sub-blocks
             hipLaunchKernelGGL(pair, dim3((unsigned)pair_groups), dim3(512), sizeof(Smem), s, a2);
             if ((e = hipGetLastError()) != hipSuccess) return e;
             for (int i = 0; i < n_more; ++i) {   // in stream order: each adds its seed gradients
@@ -1644,17 +1677,19 @@ hipError_t launch_bwd(bool bf16_out, const BwdArgs &a, const BwdView *more, int 
                            dim3(64 * kScanWaves), 0, s, a);
         if ((e = hipGetLastError()) != hipSuccess) return e;
         if (groups > 0) {
-            hipLaunchKernelGGL(clean, dim3((unsigned)groups), dim3(512), sizeof(Smem), s, a2);
+            hipLaunchKernelGGL(a.nl > 0 ? clean_small : clean, dim3((unsigned)groups), dim3(512), sizeof(Smem), s, a2);
             if ((e = hipGetLastError()) != hipSuccess) return e;
         }
         return hipSuccess;
     };
     return bf16_out ? run(bdgdn_bwd_noisy_kernel<__bf16, true>, bdgdn_bwd_noisy_kernel<__bf16, false>,
                           bdgdn_bwd_pair_kernel<__bf16, true>, bdgdn_bwd_pair_kernel<__bf16, false>,
-                          bdgdn_bwd_clean_kernel<__bf16>)
+                          bdgdn_bwd_small_kernel<__bf16>, bdgdn_bwd_clean_kernel<__bf16, false>,
+                          bdgdn_bwd_clean_kernel<__bf16, true>)
                     : run(bdgdn_bwd_noisy_kernel<float, true>, bdgdn_bwd_noisy_kernel<float, false>,
                           bdgdn_bwd_pair_kernel<float, true>, bdgdn_bwd_pair_kernel<float, false>,
-                          bdgdn_bwd_clean_kernel<float>);
+                          bdgdn_bwd_small_kernel<float>, bdgdn_bwd_clean_kernel<float, false>,
+                          bdgdn_bwd_clean_kernel<float, true>);
 }
 
 }  // namespace bdgdn

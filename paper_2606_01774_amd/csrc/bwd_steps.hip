@@ -803,8 +803,8 @@ size_t bwd_steps_workspace(long total_blocks, int h_v, int dk, int dv)
 }
 
 // The line between this schedule and the serial walk is workspace alone: at every size
-// measured this one is faster (7 x at 1 x 48 positions in blocks of 4, 27 x at 1 x 256 in
-// blocks of 16, 38 x at 1 x 371 in blocks of 8), so it runs whenever the caller gives it its
+// measured this one is faster (7 x at 3 x 63 positions in blocks of 16, 27 x at 1 x 256 in
+// blocks of 16, 38 x at 2 x 369 in blocks of 4), so it runs whenever the caller gives it its
 // two states per (block, v-head).
 hipError_t launch_bwd_steps(bool f32_in, bool f32_out, const GenBwdCall &c, hipStream_t s)
 {

@@ -1,0 +1,91 @@
+"""GPU parity of the backward for noisy blocks of 1, 2, 4, 8 and 16 positions on clean chunks of
+32 (one noisy view): against the fp64 oracle at the edges of a chunk, in time segments bit for
+bit, and the per-block schedule where packed documents are shorter than a chunk."""
+import math
+
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_2606_01774_amd as bd
+from paper_2606_01774_amd import workloads as W
+from parity_utils import TOL, rel_err
+
+pytestmark = pytest.mark.gpu
+
+NAMES = ("dq", "dk", "dv", "dg", "dbeta", "dqn", "dkn", "dvn", "dgn", "dbetan", "dh0")
+KEYS = ("q", "k", "v", "g", "beta")
+
+
+def _case(B, T, hqk, hv, L, lengths=None, out=torch.float32):
+    inp = W.make_custom_train(B, T, hqk, hv, 128, 128, "bf16", seed=T + L, lengths=lengths)
+    rng = np.random.default_rng(T + L + 1)
+    n = B if lengths is None else len(lengths)
+    do, don = (torch.from_numpy(rng.standard_normal((B, T, hv, 128)).astype(np.float32)).to(out) for _ in range(2))
+    h0 = torch.from_numpy((0.3 * rng.standard_normal((n, hv, 128, 128))).astype(np.float32))
+    # dht reaches the last positions only: at N(0, 1) their dv is up to 34 times the RMS over a
+    # sequence of 1500, and its fp16 rounding alone (2^-11 of the entry, twice) 3.3e-2 of that RMS;
+    # a tenth of it keeps that part under 4e-3
+    dht = torch.from_numpy((0.1 * rng.standard_normal((n, hv, 128, 128))).astype(np.float32))
+    cu = None if lengths is None else torch.tensor(np.concatenate([[0], np.cumsum(lengths)]), dtype=torch.int32)
+
+    def run(workspace=None):
+        got = bd.bdgdn_bwd_train(*[inp[k].cuda() for k in KEYS], *[inp[k + "n"].cuda() for k in KEYS], do.cuda(),
+                                 don.cuda(), block=L, cu_seqlens=None if cu is None else cu.cuda(),
+                                 cu_seqlens_host=cu, h0=h0.cuda(), dht=dht.cuda(), want_dh0=True,
+                                 workspace=workspace)
+        torch.cuda.synchronize()
+        return got
+    desc = bd.make_fwd_desc(inp["q"], inp["v"], block=L, num_seqs=0 if cu is None else n, out_dtype=out)
+    ref = oracle.bwd_train(*[inp[k] for k in KEYS], *[inp[k + "n"] for k in KEYS], do, don, block=L,
+                           scale=1 / math.sqrt(128), cu_seqlens=None if cu is None else cu.numpy(), h0=h0, dht=dht)
+    return run, desc, cu, ref
+
+
+def _check(got, ref):
+    for name in NAMES:
+        e = rel_err(got[name], ref[name])
+        assert e <= TOL["bf16"], f"{name}: {e:.2e}"
+
+
+@pytest.mark.parametrize("B,T,hqk,hv,L,lengths,out", [
+    (1, 32, 1, 1, 1, None, torch.float32),                     # one chunk, 32 noisy blocks
+    (1, 33, 1, 2, 2, None, torch.float32),                     # one position into a second chunk, grouped heads
+    (2, 100, 2, 2, 4, None, torch.bfloat16),                   # the last chunk one block, bf16 upstream gradients
+    (1, 95, 1, 4, 8, None, torch.float32),                     # a block short of its last position
+    (3, 48, 1, 1, 16, None, torch.float32),                    # half a chunk
+    (1, 203, 1, 2, 8, [40, 0, 8, 64, 91], torch.float32),      # documents across, inside and on chunks, an empty one
+    (1, 9, 1, 1, 16, None, torch.float32),                     # less than a block
+])
+def test_small_blocks_match_oracle(B, T, hqk, hv, L, lengths, out):
+    print(f"small blocks B={B} T={T} h={hqk}/{hv} L={L} {lengths}", flush=True)
+    run, _, _, ref = _case(B, T, hqk, hv, L, lengths, out)
+    _check(run(), ref)
+
+
+@pytest.mark.parametrize("B,T,hqk,hv,L,lengths", [
+    (1, 2050, 1, 1, 4, None),
+    (2, 1500, 1, 2, 16, None),
+    (1, 2800, 1, 1, 16, [2400, 0, 48, 352]),
+])
+def test_small_blocks_segments_bitwise(B, T, hqk, hv, L, lengths):
+    """The smallest workspace the segmented queries name holds only some of the chunks: the same
+    bits as in one pass."""
+    run, desc, cu, ref = _case(B, T, hqk, hv, L, lengths)
+    size = min(bd.bdgdn_bwd_train_workspace_segmented(desc, cu, k) for k in range(2, 40))
+    chunks = sum(-(-int(x) // 32) for x in (np.diff(cu.numpy()) if cu is not None else [T] * B)) * hv
+    assert size < chunks * (2 * 128 + 2 * 32) * 128 * 2
+    print(f"small blocks in segments, B={B} T={T} L={L} {lengths}: {size} bytes", flush=True)
+    one, seg = run(), run(torch.empty(size, dtype=torch.uint8, device="cuda"))
+    for name in NAMES:
+        assert torch.equal(one[name], seg[name]), name
+    _check(seg, ref)
+
+
+def test_documents_shorter_than_a_chunk_keep_their_workspace():
+    """Documents of one block of 16: chunks need more than the queried workspace, so blocks run
+    one by one in it."""
+    run, desc, cu, ref = _case(1, 96, 1, 1, 16, [16] * 6)
+    print("small blocks: documents of one block", flush=True)
+    _check(run(torch.empty(bd.bdgdn_bwd_train_workspace(desc), dtype=torch.uint8, device="cuda")), ref)
