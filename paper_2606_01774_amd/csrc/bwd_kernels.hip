@@ -766,11 +766,11 @@ namespace {
 // no atomics, nothing to clear.  Returns the unit's index in the per-(block, v-head) arrays.
 __device__ __forceinline__ long unit_of(const BwdArgs &a, long t, long &gblk, int &h, int &hq, int &i)
 {
-    const int r = a.h_v / a.h_qk;
-    const long gi = t / r;
-    i = (int)(t % r);
-    gblk = gi / a.h_qk;
-    hq = (int)(gi % a.h_qk);
+    // a launch has fewer than 2^32 units: 32-bit division
+    const unsigned r = a.h_v / a.h_qk, ti = (unsigned)t, gi = ti / r;
+    i = (int)(ti % r);
+    gblk = gi / (unsigned)a.h_qk;
+    hq = (int)(gi % (unsigned)a.h_qk);
     h = hq * r + i;
     return gblk * a.h_v + h;
 }
@@ -809,8 +809,9 @@ __device__ __forceinline__ void block_unit(const BwdArgs &a, long gblk, int &n, 
         const long rem = a.cu[lo + 1] - p0;
         nvalid = (int)(rem < a.L ? rem : a.L);
     } else {
-        n = (int)(gblk / a.nblk);
-        const int b = (int)(gblk % a.nblk);
+        // a launch has fewer than 2^32 units: 32-bit division
+        n = (int)((unsigned)gblk / (unsigned)a.nblk);
+        const int b = (int)((unsigned)gblk % (unsigned)a.nblk);
         p0 = (long)n * a.T + (long)b * a.L;
         const int rem = a.T - b * a.L;
         nvalid = rem < a.L ? rem : a.L;
@@ -927,106 +928,7 @@ __device__ __forceinline__ void clean_prep(Smem &sm, const BwdArgs &a, float gx,
     __syncthreads();
 }
 
-// Phase 1: every noisy block: its gradients and its seed's gradient, plus (PREP) the
-// dh-independent part of the clean block of the same position (clean_prep, run first: it
-// needs no seed); both enter the state gradient at the block's start, whose sum is written
-// to cterm (fp16, the precision of the dh it joins; per (block, v-head) 64 tiles of 16 x 16
-// in row-major tile order, each tile stored lane-major in the MFMA result layout: lane
-// 16 g + r holds rows 4 g .. 4 g + 3 of column r as one 8-byte vector, the layout both
-// this kernel and the scan hold it in registers).  Without PREP (the further noisy views of
-// the complementary-view backward, each seeded from the same clean state) the seed's
-// gradient is added to cterm.  Persistent: one 160 KB workgroup per CU walks the units (global block,
-// v-head) u = blockIdx.x, + gridDim.x, ...; the next unit's clean rows are loaded while the
-// current unit finishes and staged into arrays it no longer uses, and each unit's seed and
-// noisy rows are in flight while its clean prep runs.
-template <typename Od, bool PREP>
-__global__ void __launch_bounds__(512) bdgdn_bwd_noisy_kernel(BwdArgs a)
-{
-    extern __shared__ __align__(16) unsigned char smem_raw[];
-    Smem &sm = *reinterpret_cast<Smem *>(smem_raw);
-    // workgroup w takes the (block, q/k head) groups w, w + gridDim.x, ..., each as its r
-    // consecutive units (unit_of)
-    const int r = a.h_v / a.h_qk;
-    long u = (long)blockIdx.x * r;
-    auto next_unit = [&](long t) { return (t + 1) % r ? t + 1 : t + 1 + (long)(gridDim.x - 1) * r; };
-    float cg = 0.f, cb = 0.f;   // the clean gate and step size of position tid of unit u
-    if constexpr (PREP) {
-        const int tid = threadIdx.x;
-        int n, nvalid;
-        long p0;
-        long gb;
-        int h, hq, vi;
-        unit_of(a, u, gb, h, hq, vi);
-        block_unit(a, gb, n, p0, nvalid);
-        const BlockRows<Od, false> cin =
-            load_block<Od, false>(stream_ptrs<Od>(a, false, p0, h, hq), a.h_qk, a.h_v, nvalid, tid);
-        store_rows(sm.R, cin.q, tid);
-        store_rows(sm.dDl, cin.k, tid);
-        store_rows(sm.dO, cin.dout, tid, a.range[0]);
-        cg = cin.g;
-        cb = cin.b;
-    }
-    for (;;) {
-        // the thread index made opaque per unit, so that the body's lane-dependent addresses
-        // are recomputed rather than hoisted out of the loop (where they would stay live)
-        int tid = threadIdx.x;
-        asm volatile("" : "+v"(tid));
-        const int lane = tid & 63, wave = tid >> 6, g4 = lane >> 4, rr = lane & 15;
-        const long un = next_unit(u);
-        const bool more = un < a.n_units;
-        int n, nvalid;
-        long p0;
-        long gb;
-        int h, hq, vi;
-        const long uw = unit_of(a, u, gb, h, hq, vi);   // the unit's workspace index
-        block_unit(a, gb, n, p0, nvalid);
-        const StreamPtrs pn = stream_ptrs<Od>(a, true, p0, h, hq);
-        const SeedRegs seed = load_seed(a.seeds + (size_t)uw * DD * DD, tid);
-        const BlockRows<Od, true> nin = load_block<Od, true>(pn, a.h_qk, a.h_v, nvalid, tid);
-        float acc[8][4];
-#pragma unroll
-        for (int tm = 0; tm < 8; ++tm)
-#pragma unroll
-            for (int j = 0; j < 4; ++j) acc[tm][j] = 0.f;
-        if constexpr (PREP) clean_prep(sm, a, cg, cb, acc, a.uk + uw * NP * DD, a.gnb + uw, tid);
-        store_seed(sm.S0, seed, tid);   // made visible by block_bwd's first barrier
-        BlockRows<Od, false> nxt;
-        block_bwd<Mode::Noisy, Od>(
-            sm, pn, a, nvalid, nin, acc, tid, vi > 0,
-            [&] {
-                if (PREP && more) {
-                    int n2, nv2;
-                    long q0;
-                    long gb2;
-                    int h2, hq2, vi2;
-                    unit_of(a, un, gb2, h2, hq2, vi2);
-                    block_unit(a, gb2, n2, q0, nv2);
-                    nxt = load_block<Od, false>(stream_ptrs<Od>(a, false, q0, h2, hq2), a.h_qk, a.h_v, nv2, tid);
-                }
-            },
-            [&] {
-                if (PREP && more) {
-                    store_rows(sm.R, nxt.q, tid);
-                    store_rows(sm.dDl, nxt.k, tid);
-                    store_rows(sm.dO, nxt.dout, tid, a.range[0]);
-                    cg = nxt.g;
-                    cb = nxt.b;
-                }
-            });
-        f16x4 *dst = reinterpret_cast<f16x4 *>(a.cterm + (size_t)uw * DD * DD) + wave * 64 + lane;
-#pragma unroll
-        for (int tm = 0; tm < 8; ++tm) {
-            f16x4 *p = dst + tm * 8 * 64;   // tile (tm, wave)
-            f16x4 v;
-            if constexpr (!PREP) v = *p;
-#pragma unroll
-            for (int j = 0; j < 4; ++j) v[j] = (_Float16)(PREP ? acc[tm][j] : (float)v[j] + acc[tm][j]);
-            *p = v;
-        }
-        if (!more) break;
-        u = un;
-    }
-}
+#include "bwd_block.hpp"
 
 // Phase 1 for noisy blocks of two sub-blocks (blocks of 2 L positions, L = a.L <= 32, the
 // clean stream cut into sub-blocks of L): one workgroup per (block, v-head).  The noisy block
@@ -1224,43 +1126,6 @@ __global__ void __launch_bounds__(512) bdgdn_bwd_pair_kernel(BwdArgs a)
         int tid = threadIdx.x;
         asm volatile("" : "+v"(tid));
         pair_unit<Od, PREP>(sm, a, (long)blockIdx.x * r + i, tid);
-    }
-}
-
-// Phase 3: every clean block, in parallel, from its seed and the gradient at its end (dh,
-// written by the scan); one workgroup per (block, q/k head).  SMALL: with the shares of the
-// chunk's small noisy blocks (block_bwd).
-template <typename Od, bool SMALL>
-__global__ void __launch_bounds__(512) bdgdn_bwd_clean_kernel(BwdArgs a)
-{
-    extern __shared__ __align__(16) unsigned char smem_raw[];
-    Smem &sm = *reinterpret_cast<Smem *>(smem_raw);
-    const int r = a.h_v / a.h_qk;
-    for (int i = 0; i < r; ++i) {   // the v-heads of this (block, q/k head) in turn
-        int tid = threadIdx.x;       // opaque per unit, as in the noisy kernel
-        asm volatile("" : "+v"(tid));
-        long gblk;
-        int h, hq, vi;
-        unit_of(a, (long)blockIdx.x * r + i, gblk, h, hq, vi);
-        int n, nvalid;
-        long p0;
-        block_unit(a, gblk, n, p0, nvalid);
-        const size_t so = ((size_t)gblk * a.h_v + h) * DD * DD;
-        const StreamPtrs pc = stream_ptrs<Od>(a, false, p0, h, hq);
-        const SeedRegs seed = load_seed(a.seeds + so, tid);
-        const SeedRegs dh = load_seed(a.dh + so, tid);   // fp16, tile-native
-        const BlockRows<Od, true> in = load_block<Od, true>(pc, a.h_qk, a.h_v, nvalid, tid);
-        store_seed(sm.S0, seed, tid);
-        store_tiles(sm.dS, dh, tid);
-        float no_acc[8][4] = {};   // the clean stream forms no dS0
-        // its first barrier covers S0, dS; its last one the next v-head's stores
-        f16x4 xd[2];
-        if constexpr (SMALL) {
-            const f16x4 *x = reinterpret_cast<const f16x4 *>(a.xd + ((size_t)gblk * a.h_v + h) * NP * DD) + tid;
-            xd[0] = x[0];
-            xd[1] = x[8 * 64];
-        }
-        block_bwd<Mode::Clean, Od, SMALL>(sm, pc, a, nvalid, in, no_acc, tid, vi > 0, [] {}, [] {}, xd);
     }
 }
 
@@ -1635,7 +1500,7 @@ hipError_t launch_bwd(bool bf16_out, const BwdArgs &a, const BwdView *more, int 
         b.dqn = w.dq; b.dkn = w.dk; b.dvn = w.dv; b.dgn = w.dg; b.dbn = w.db;
         return b;
     };
-    // the persistent noisy kernels: one workgroup per CU (their LDS allows no more)
+    // the persistent small-block kernel: one workgroup per CU (its LDS allows no more)
     int dev = 0, n_cu = 0;
     hipError_t err = hipGetDevice(&dev);
     if (err == hipSuccess) err = hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev);
@@ -1644,13 +1509,12 @@ hipError_t launch_bwd(bool bf16_out, const BwdArgs &a, const BwdView *more, int 
     auto run = [&](auto noisy, auto noisy_more, auto pair, auto pair_more, auto small, auto clean, auto clean_small) {
         for (const void *f : {reinterpret_cast<const void *>(noisy), reinterpret_cast<const void *>(noisy_more),
                               reinterpret_cast<const void *>(pair), reinterpret_cast<const void *>(pair_more),
-                              reinterpret_cast<const void *>(clean), reinterpret_cast<const void *>(clean_small)}) {
-            const hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)sizeof(Smem));
+                              reinterpret_cast<const void *>(small), reinterpret_cast<const void *>(clean),
+                              reinterpret_cast<const void *>(clean_small)}) {
+            const hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
             if (e != hipSuccess) return e;
         }
-        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(small),
-                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)sizeof(SmallSmem));
-        if (e != hipSuccess) return e;
+        hipError_t e;
         if (a.nl > 0) {   // small noisy blocks in clean chunks
             if (groups > 0) {
                 hipLaunchKernelGGL(small, dim3(pgrid), dim3(512), sizeof(SmallSmem), s, a2);
@@ -1665,10 +1529,11 @@ hipError_t launch_bwd(bool bf16_out, const BwdArgs &a, const BwdView *more, int 
                 if ((e = hipGetLastError()) != hipSuccess) return e;
             }
         } else if (groups > 0) {
-            hipLaunchKernelGGL(noisy, dim3(pgrid), dim3(512), sizeof(Smem), s, a2);
+            hipLaunchKernelGGL(noisy, dim3((unsigned)groups), dim3(512), sizeof(NoisySmem), s, a2);
             if ((e = hipGetLastError()) != hipSuccess) return e;
             for (int i = 0; i < n_more; ++i) {   // in stream order: each adds its seed gradients
-                hipLaunchKernelGGL(noisy_more, dim3(pgrid), dim3(512), sizeof(Smem), s, with_view(more[i]));
+                hipLaunchKernelGGL(noisy_more, dim3((unsigned)groups), dim3(512), sizeof(NoisySmem), s,
+                                   with_view(more[i]));
                 if ((e = hipGetLastError()) != hipSuccess) return e;
             }
         }
@@ -1677,7 +1542,8 @@ hipError_t launch_bwd(bool bf16_out, const BwdArgs &a, const BwdView *more, int 
                            dim3(64 * kScanWaves), 0, s, a);
         if ((e = hipGetLastError()) != hipSuccess) return e;
         if (groups > 0) {
-            hipLaunchKernelGGL(a.nl > 0 ? clean_small : clean, dim3((unsigned)groups), dim3(512), sizeof(Smem), s, a2);
+            hipLaunchKernelGGL(a.nl > 0 ? clean_small : clean, dim3((unsigned)groups), dim3(512),
+                               sizeof(CleanSmem), s, a2);
             if ((e = hipGetLastError()) != hipSuccess) return e;
         }
         return hipSuccess;

@@ -58,31 +58,6 @@ struct SmallSmem {
 static_assert(sizeof(SmallSmem) <= 160 * 1024, "one workgroup's LDS");
 static_assert(2 * NP * LDF * 4 <= NP * LDH * 2, "two fp32 matrices in the room of a row block");
 
-// a 16 x 32 by 32 x 16 product from operand quads over k = 0 .. 15 and 16 .. 31 (one
-// 16x16x32 step: A and B agree on which k each slot holds)
-__device__ __forceinline__ f32x4 mfma2(f16x4 a0, f16x4 a1, f16x4 b0, f16x4 b1, f32x4 c)
-{
-    const f16x8 a = __builtin_shufflevector(a0, a1, 0, 1, 2, 3, 4, 5, 6, 7);
-    const f16x8 b = __builtin_shufflevector(b0, b1, 0, 1, 2, 3, 4, 5, 6, 7);
-    return __builtin_amdgcn_mfma_f32_16x16x32_f16(a, b, c, 0, 0, 0);
-}
-// rows m0 .. of a [32][32] matrix, and rows m0 .. of its transpose, times the k-quads b
-__device__ __forceinline__ f32x4 apply(const _Float16 *X, int m0, const f16x4 (&b)[2], f32x4 c, int lane)
-{
-    return mfma2(op_row(X, LDM, m0, 0, lane), op_row(X, LDM, m0, 16, lane), b[0], b[1], c);
-}
-__device__ __forceinline__ f32x4 apply_t(const _Float16 *X, int ld, int m0, const f16x4 (&b)[2], f32x4 c, int lane)
-{
-    return mfma2(op_tr(X, ld, 0, m0, lane), op_tr(X, ld, 16, m0, lane), b[0], b[1], c);
-}
-__device__ __forceinline__ f32x4 f4(f16x4 v) { return f32x4{(float)v[0], (float)v[1], (float)v[2], (float)v[3]}; }
-// a C tile (rows m0 + 4 g + j, column c) into a row-major fp16 matrix
-__device__ __forceinline__ void put_tile(_Float16 *X, int ld, int m0, int c, f16x4 v, int g4)
-{
-#pragma unroll
-    for (int j = 0; j < 4; ++j) X[(m0 + 4 * g4 + j) * ld + c] = v[j];
-}
-
 // One unit's inputs in registers.
 template <typename Od> struct SmallRows {
     BlockRows<Od, true> c, n;
