@@ -13,6 +13,7 @@ shape that flattens to rows), v, o ``[rows, h_v, d_v]``, g (log-gate), beta
 from __future__ import annotations
 
 import ctypes
+import functools
 import math
 import os
 
@@ -172,6 +173,9 @@ def bdgdn_status_string(status: int) -> str:
 _DT = {torch.bfloat16: BDGDN_BF16, torch.float32: BDGDN_F32}
 
 
+_F32, _I32, _Tensor = torch.float32, torch.int32, torch.Tensor
+
+
 def _ptr(t):
     if t is None:
         return None
@@ -190,10 +194,25 @@ def _dev(t, name, dtype=None):
     return t
 
 
+def _p(t, name, dtype=None):
+    """The address of a device tensor that _dev accepts (None for None).  A call of a serving
+    step is as short as its marshalling (12 us a call against a 6 us kernel with a ctypes
+    object per argument, a descriptor and a stream object per call), so the common case is one
+    chained test and plain integers go to ctypes."""
+    if type(t) is _Tensor and t.is_cuda and t.is_contiguous() and (dtype is None or t.dtype is dtype):
+        return t.data_ptr()
+    return None if _dev(t, name, dtype) is None else t.data_ptr()
+
+
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream(stream):
-    if stream is None:
-        stream = torch.cuda.current_stream()
-    return ctypes.c_void_p(stream.cuda_stream)
+    if stream is not None:
+        return stream.cuda_stream
+    if _raw_stream is not None:
+        return _raw_stream(torch.cuda.current_device())
+    return torch.cuda.current_stream().cuda_stream
 
 
 def _check(status, where):
@@ -212,6 +231,42 @@ def make_fwd_desc(q, v, *, block, scale=None, batch=None, num_seqs=0, route=BDGD
                    float(scale), _DT.get(q.dtype, -1), int(route), _DT.get(out_dtype, -1))
 
 
+# A call's descriptor follows from its sizes, types and options alone and is only read by the
+# library: the last few hundred are kept, with the workspace sizes that depend on them.
+@functools.lru_cache(maxsize=512)
+def _fwd_plan(batch, seqlen, num_seqs, h_qk, h_v, d_k, d_v, block, scale, dtype, route, out_dtype):
+    desc = FwdDesc(batch, seqlen, num_seqs, h_qk, h_v, d_k, d_v, block, scale, _DT.get(dtype, -1), route,
+                   _DT.get(out_dtype, -1))
+    return desc, ctypes.byref(desc), {}
+
+
+def _fwd_desc(q, v, block, scale, num_seqs, out_dtype, route=BDGDN_ROUTE_FUSED):
+    """(descriptor, reference to it, workspace sizes by query) of 4-D tensors, as make_fwd_desc."""
+    B, T, h_qk, d_k = q.shape
+    vs = v.shape
+    return _fwd_plan(B, T, num_seqs, h_qk, vs[2], d_k, vs[3], int(block),
+                     1.0 / math.sqrt(d_k) if scale is None else float(scale), q.dtype, int(route), out_dtype)
+
+
+def _plan_bytes(plan, query):
+    size = plan[2].get(query)
+    if size is None:
+        size = plan[2][query] = query(plan[0])
+    return size
+
+
+@functools.lru_cache(maxsize=512)
+def _serve_plan(R, L, h_qk, h_v, d_k, d_v, scale, dtype, out_dtype):
+    desc = ServeDesc(R, h_qk, h_v, d_k, d_v, L, scale, _DT.get(dtype, -1), _DT.get(out_dtype, -1))
+    return ctypes.byref(desc)
+
+
+@functools.lru_cache(maxsize=512)
+def _conv_plan(B, T, num_seqs, channels, width, block, activation, dtype):
+    desc = ConvDesc(B, T, num_seqs, channels, width, block, activation, _DT.get(dtype, -1))
+    return desc, ctypes.byref(desc), {}
+
+
 def bdgdn_fwd_train_workspace(desc: FwdDesc) -> int:
     return int(load_library().bdgdn_fwd_train_workspace(ctypes.byref(desc)))
 
@@ -224,12 +279,11 @@ def bdgdn_fwd_train(q, k, v, g, beta, qn, kn, vn, gn, betan, *, block, scale=Non
     cu_seqlens [N+1] int32 on the device; cu_seqlens_host may be given to avoid a
     device-to-host copy).  Outputs are ``out_dtype`` (fp32 by default; bf16 is
     offered for bf16 inputs).  Returns (o, on, ht)."""
-    lib = load_library()
+    lib = _lib or load_library()
     dt = q.dtype
-    for name, t in (("q", q), ("k", k), ("v", v), ("qn", qn), ("kn", kn), ("vn", vn)):
-        _dev(t, name, dt)
-    for name, t in (("g", g), ("beta", beta), ("gn", gn), ("betan", betan)):
-        _dev(t, name, torch.float32)
+    pq, pk, pv = _p(q, "q", dt), _p(k, "k", dt), _p(v, "v", dt)
+    pqn, pkn, pvn = _p(qn, "qn", dt), _p(kn, "kn", dt), _p(vn, "vn", dt)
+    pg, pb, pgn, pbn = _p(g, "g", _F32), _p(beta, "beta", _F32), _p(gn, "gn", _F32), _p(betan, "betan", _F32)
     if q.dim() != 4 or v.dim() != 4:
         raise ValueError("q, k, v must be [B, T, heads, dim]")
     num_seqs = 0
@@ -244,29 +298,25 @@ def bdgdn_fwd_train(q, k, v, g, beta, qn, kn, vn, gn, betan, *, block, scale=Non
             raise ValueError("cu_seqlens_host and cu_seqlens differ in length")
     if o is not None:
         out_dtype = o.dtype
-    desc = make_fwd_desc(q, v, block=block, scale=scale, num_seqs=num_seqs, route=route,
-                         out_dtype=out_dtype)
+    plan = _fwd_desc(q, v, block, scale, num_seqs, out_dtype, route)
     if o is None:
         o = torch.empty(v.shape, dtype=out_dtype, device=v.device)
     if on is None:
         on = torch.empty(vn.shape, dtype=out_dtype, device=vn.device)
-    _dev(o, "o", out_dtype)
-    _dev(on, "on", out_dtype)
+    po, pon = _p(o, "o", out_dtype), _p(on, "on", out_dtype)
     units = num_seqs if num_seqs else q.shape[0]
     if ht is None and want_ht:
         ht = torch.empty(units, v.shape[2], q.shape[3], v.shape[3], device=q.device,
                          dtype=torch.float32)
-    _dev(ht, "ht", torch.float32)
-    _dev(h0, "h0", torch.float32)
-    ws_bytes = bdgdn_fwd_train_workspace(desc)
+    pht, ph0 = _p(ht, "ht", _F32), _p(h0, "h0", _F32)
+    ws_bytes = _plan_bytes(plan, bdgdn_fwd_train_workspace)
     if workspace is None and ws_bytes:
         workspace = torch.empty(ws_bytes, dtype=torch.uint8, device=q.device)
     ws_size = 0 if workspace is None else workspace.numel() * workspace.element_size()
     st = lib.bdgdn_fwd_train(
-        ctypes.byref(desc), _ptr(q), _ptr(k), _ptr(v), _ptr(g), _ptr(beta),
-        _ptr(qn), _ptr(kn), _ptr(vn), _ptr(gn), _ptr(betan),
-        _ptr(cu_seqlens), None if cu_h is None else ctypes.c_void_p(cu_h.data_ptr()),
-        _ptr(h0), _ptr(o), _ptr(on), _ptr(ht), _ptr(workspace), ws_size, _stream(stream))
+        plan[1], pq, pk, pv, pg, pb, pqn, pkn, pvn, pgn, pbn, None if cu_seqlens is None else cu_seqlens.data_ptr(),
+        None if cu_h is None else cu_h.data_ptr(), ph0, po, pon, pht,
+        None if workspace is None else workspace.data_ptr(), ws_size, _stream(stream))
     _check(st, "bdgdn_fwd_train")
     return o, on, ht
 
@@ -364,14 +414,13 @@ def bdgdn_bwd_train(q, k, v, g, beta, qn, kn, vn, gn, betan, do, don, *, block, 
     output tensors (same names).  Without ``workspace``, one of the full size is allocated,
     or with ``segments`` that of that many time segments (the library then runs the
     segmented schedule)."""
-    lib = load_library()
+    lib = _lib or load_library()
     dt = q.dtype
-    for name, t in (("q", q), ("k", k), ("v", v), ("qn", qn), ("kn", kn), ("vn", vn)):
-        _dev(t, name, dt)
-    for name, t in (("g", g), ("beta", beta), ("gn", gn), ("betan", betan)):
-        _dev(t, name, torch.float32)
-    _dev(do, "do")
-    _dev(don, "don", do.dtype)
+    pq, pk, pv = _p(q, "q", dt), _p(k, "k", dt), _p(v, "v", dt)
+    pqn, pkn, pvn = _p(qn, "qn", dt), _p(kn, "kn", dt), _p(vn, "vn", dt)
+    pg, pb, pgn, pbn = _p(g, "g", _F32), _p(beta, "beta", _F32), _p(gn, "gn", _F32), _p(betan, "betan", _F32)
+    pdo = _p(do, "do")
+    pdon = _p(don, "don", do.dtype)
     num_seqs = 0
     cu_h = None
     if cu_seqlens is not None:
@@ -380,29 +429,26 @@ def bdgdn_bwd_train(q, k, v, g, beta, qn, kn, vn, gn, betan, do, don, *, block, 
         if cu_seqlens_host is None:
             cu_seqlens_host = cu_seqlens.cpu()
         cu_h = torch.as_tensor(cu_seqlens_host, dtype=torch.int32).contiguous()
-    desc = make_fwd_desc(q, v, block=block, scale=scale, num_seqs=num_seqs, out_dtype=do.dtype)
+    plan = _fwd_desc(q, v, block, scale, num_seqs, do.dtype)
     out = {} if grads is None else dict(grads)
-    like = {"dq": q, "dk": k, "dv": v, "dg": g, "dbeta": beta, "dqn": qn, "dkn": kn, "dvn": vn, "dgn": gn,
-            "dbetan": betan}
-    for name in _BWD_NAMES:
+    device, ptrs = q.device, []
+    for name, t in zip(_BWD_NAMES, (q, k, v, g, beta, qn, kn, vn, gn, betan)):
         if name not in out:
-            out[name] = torch.empty(like[name].shape, dtype=torch.float32, device=q.device)
-        _dev(out[name], name, torch.float32)
+            out[name] = x = torch.empty(t.shape, dtype=_F32, device=device)
+            ptrs.append(x.data_ptr())
+        else:
+            ptrs.append(_p(out[name], name, _F32))
     units = num_seqs if num_seqs else q.shape[0]
     if want_dh0 and "dh0" not in out:
         out["dh0"] = torch.empty(units, v.shape[2], q.shape[3], v.shape[3], dtype=torch.float32, device=q.device)
-    _dev(h0, "h0", torch.float32)
-    _dev(dht, "dht", torch.float32)
+    ph0, pdht = _p(h0, "h0", _F32), _p(dht, "dht", _F32)
     if workspace is None:
-        workspace = _bwd_workspace(desc, cu_h, segments, bdgdn_bwd_train_workspace(desc), q.device)
+        workspace = _bwd_workspace(plan[0], cu_h, segments, _plan_bytes(plan, bdgdn_bwd_train_workspace), device)
     ws_size = 0 if workspace is None else workspace.numel() * workspace.element_size()
     st = lib.bdgdn_bwd_train(
-        ctypes.byref(desc), _ptr(q), _ptr(k), _ptr(v), _ptr(g), _ptr(beta),
-        _ptr(qn), _ptr(kn), _ptr(vn), _ptr(gn), _ptr(betan),
-        _ptr(cu_seqlens), None if cu_h is None else ctypes.c_void_p(cu_h.data_ptr()),
-        _ptr(h0), _ptr(do), _ptr(don), _ptr(dht),
-        *[_ptr(out[n]) for n in _BWD_NAMES], _ptr(out.get("dh0")),
-        _ptr(workspace), ws_size, _stream(stream))
+        plan[1], pq, pk, pv, pg, pb, pqn, pkn, pvn, pgn, pbn, None if cu_seqlens is None else cu_seqlens.data_ptr(),
+        None if cu_h is None else cu_h.data_ptr(), ph0, pdo, pdon, pdht, *ptrs, _ptr(out.get("dh0")),
+        None if workspace is None else workspace.data_ptr(), ws_size, _stream(stream))
     _check(st, "bdgdn_bwd_train")
     return out
 
@@ -478,34 +524,27 @@ def bdgdn_bwd_train_views(q, k, v, g, beta, views, do, *, block, scale=None, cu_
 
 
 def _serve_desc(q, v, scale, out_dtype):
+    """A reference to the serving descriptor of blocks q [R, L, h_qk, d_k], v [R, L, h_v, d_v]."""
     R, L, h_qk, d_k = q.shape
-    h_v, d_v = v.shape[2], v.shape[3]
-    if scale is None:
-        scale = 1.0 / math.sqrt(d_k)
-    return ServeDesc(R, h_qk, h_v, d_k, d_v, L, float(scale), _DT.get(q.dtype, -1),
-                     _DT.get(out_dtype, -1))
+    vs = v.shape
+    return _serve_plan(R, L, h_qk, vs[2], d_k, vs[3], 1.0 / math.sqrt(d_k) if scale is None else float(scale), q.dtype,
+                       out_dtype)
 
 
 def bdgdn_denoise_step(state_pool, q, k, v, g, beta, *, scale=None, slot=None, o=None,
                        out_dtype=torch.float32, stream=None):
     """Block-end readout of R blocks ([R, L, h, d] tensors) seeded from
     state_pool[slot[r]]; the pool is only read.  Returns o."""
-    lib = load_library()
+    lib = _lib or load_library()
     dt = q.dtype
-    _dev(state_pool, "state_pool", torch.float32)
-    for name, t in (("q", q), ("k", k), ("v", v)):
-        _dev(t, name, dt)
-    _dev(g, "g", torch.float32)
-    _dev(beta, "beta", torch.float32)
-    _dev(slot, "slot", torch.int32)
+    pool, pq, pk, pv = _p(state_pool, "state_pool", _F32), _p(q, "q", dt), _p(k, "k", dt), _p(v, "v", dt)
+    pg, pb, ps = _p(g, "g", _F32), _p(beta, "beta", _F32), _p(slot, "slot", _I32)
     if o is not None:
         out_dtype = o.dtype
     if o is None:
         o = torch.empty(v.shape, dtype=out_dtype, device=v.device)
-    _dev(o, "o", out_dtype)
-    desc = _serve_desc(q, v, scale, out_dtype)
-    st = lib.bdgdn_denoise_step(ctypes.byref(desc), _ptr(state_pool), _ptr(slot), _ptr(q),
-                                _ptr(k), _ptr(v), _ptr(g), _ptr(beta), _ptr(o), _stream(stream))
+    po = _p(o, "o", out_dtype)
+    st = lib.bdgdn_denoise_step(_serve_desc(q, v, scale, out_dtype), pool, ps, pq, pk, pv, pg, pb, po, _stream(stream))
     _check(st, "bdgdn_denoise_step")
     return o
 
@@ -514,22 +553,16 @@ def bdgdn_commit(state_pool, q, k, v, g, beta, *, scale=None, slot=None, o_causa
                  want_o=False, out_dtype=torch.float32, stream=None):
     """Token-causal pass over R blocks; advances state_pool[slot[r]] in place.
     Returns o_causal (or None)."""
-    lib = load_library()
+    lib = _lib or load_library()
     dt = q.dtype
-    _dev(state_pool, "state_pool", torch.float32)
-    for name, t in (("q", q), ("k", k), ("v", v)):
-        _dev(t, name, dt)
-    _dev(g, "g", torch.float32)
-    _dev(beta, "beta", torch.float32)
-    _dev(slot, "slot", torch.int32)
+    pool, pq, pk, pv = _p(state_pool, "state_pool", _F32), _p(q, "q", dt), _p(k, "k", dt), _p(v, "v", dt)
+    pg, pb, ps = _p(g, "g", _F32), _p(beta, "beta", _F32), _p(slot, "slot", _I32)
     if o_causal is not None:
         out_dtype = o_causal.dtype
     if o_causal is None and want_o:
         o_causal = torch.empty(v.shape, dtype=out_dtype, device=v.device)
-    _dev(o_causal, "o_causal", out_dtype)
-    desc = _serve_desc(q, v, scale, out_dtype)
-    st = lib.bdgdn_commit(ctypes.byref(desc), _ptr(state_pool), _ptr(slot), _ptr(q), _ptr(k),
-                          _ptr(v), _ptr(g), _ptr(beta), _ptr(o_causal), _stream(stream))
+    po = _p(o_causal, "o_causal", out_dtype)
+    st = lib.bdgdn_commit(_serve_desc(q, v, scale, out_dtype), pool, ps, pq, pk, pv, pg, pb, po, _stream(stream))
     _check(st, "bdgdn_commit")
     return o_causal
 
@@ -539,28 +572,22 @@ def bdgdn_commit_record(state_pool, q, k, v, g, beta, *, n_record, scale=None, s
     """The AR-Trust verify pass: bdgdn_commit over R blocks of L positions that also writes
     states[r, i] = the state before block position L - n_record + i.
     Returns (states [R, n_record, Hv, dk, dv] fp32, o_causal or None)."""
-    lib = load_library()
+    lib = _lib or load_library()
     dt = q.dtype
-    _dev(state_pool, "state_pool", torch.float32)
-    for name, t in (("q", q), ("k", k), ("v", v)):
-        _dev(t, name, dt)
-    _dev(g, "g", torch.float32)
-    _dev(beta, "beta", torch.float32)
-    _dev(slot, "slot", torch.int32)
+    pool, pq, pk, pv = _p(state_pool, "state_pool", _F32), _p(q, "q", dt), _p(k, "k", dt), _p(v, "v", dt)
+    pg, pb, ps = _p(g, "g", _F32), _p(beta, "beta", _F32), _p(slot, "slot", _I32)
     R, L, _, dk = q.shape
     Hv, dv = v.shape[2], v.shape[3]
     if states is None:
         states = torch.empty(R, int(n_record), Hv, dk, dv, dtype=torch.float32, device=q.device)
-    _dev(states, "states", torch.float32)
+    pst = _p(states, "states", _F32)
     if o_causal is not None:
         out_dtype = o_causal.dtype
     if o_causal is None and want_o:
         o_causal = torch.empty(v.shape, dtype=out_dtype, device=v.device)
-    _dev(o_causal, "o_causal", out_dtype)
-    desc = _serve_desc(q, v, scale, out_dtype)
-    st = lib.bdgdn_commit_record(ctypes.byref(desc), _ptr(state_pool), _ptr(slot), _ptr(q), _ptr(k),
-                                 _ptr(v), _ptr(g), _ptr(beta), _ptr(o_causal), int(n_record), _ptr(states),
-                                 _stream(stream))
+    po = _p(o_causal, "o_causal", out_dtype)
+    st = lib.bdgdn_commit_record(_serve_desc(q, v, scale, out_dtype), pool, ps, pq, pk, pv, pg, pb, po, int(n_record),
+                                 pst, _stream(stream))
     _check(st, "bdgdn_commit_record")
     return states, o_causal
 
@@ -568,16 +595,12 @@ def bdgdn_commit_record(state_pool, q, k, v, g, beta, *, n_record, scale=None, s
 def bdgdn_accept_states(state_pool, states, accept, *, block, h_qk=None, slot=None, stream=None):
     """The accept step: state_pool[slot[r]] <- states[r, accept[r]] where accept[r] <
     n_record (states [R, n_record, Hv, dk, dv] from bdgdn_commit_record; block = its L)."""
-    lib = load_library()
-    _dev(state_pool, "state_pool", torch.float32)
-    _dev(states, "states", torch.float32)
-    _dev(accept, "accept", torch.int32)
-    _dev(slot, "slot", torch.int32)
+    lib = _lib or load_library()
+    pool, pst = _p(state_pool, "state_pool", _F32), _p(states, "states", _F32)
+    pa, ps = _p(accept, "accept", _I32), _p(slot, "slot", _I32)
     R, n_record, Hv, dk, dv = states.shape
-    desc = ServeDesc(R, Hv if h_qk is None else int(h_qk), Hv, dk, dv, int(block), 1.0, BDGDN_BF16,
-                     _DT[torch.float32])
-    st = lib.bdgdn_accept_states(ctypes.byref(desc), _ptr(state_pool), _ptr(slot), _ptr(states),
-                                 int(n_record), _ptr(accept), _stream(stream))
+    desc = _serve_plan(R, int(block), Hv if h_qk is None else int(h_qk), Hv, dk, dv, 1.0, torch.bfloat16, _F32)
+    st = lib.bdgdn_accept_states(desc, pool, ps, pst, n_record, pa, _stream(stream))
     _check(st, "bdgdn_accept_states")
 
 
@@ -603,29 +626,30 @@ def make_conv_desc(x, w, *, block, activation=BDGDN_ACT_SILU, num_seqs=0):
     return ConvDesc(B, T, num_seqs, D, int(w.shape[1]), int(block), int(activation), _DT.get(x.dtype, -1))
 
 
+def _conv_desc(x, w, block, activation, num_seqs):
+    B, T, D = x.shape
+    return _conv_plan(B, T, num_seqs, D, int(w.shape[1]), int(block), int(activation), x.dtype)
+
+
 def bdgdn_shortconv_fwd(x, xn, w, bias=None, *, block, activation=BDGDN_ACT_SILU, cu_seqlens=None,
                         cu_seqlens_host=None, y=None, yn=None, stream=None):
     """Two-stream ShortConv forward.  x, xn [B, T, channels] (bf16 or fp32; packed: B == 1
     and cu_seqlens [N+1] int32 on the device), w [channels, width] fp32 (lag-i weight in
     column i), bias [channels] fp32 or None.  Returns (y, yn) of x's dtype."""
-    lib = load_library()
-    _dev(x, "x")
-    _dev(xn, "xn", x.dtype)
-    _dev(w, "w", torch.float32)
-    _dev(bias, "bias", torch.float32)
+    lib = _lib or load_library()
+    px, pxn = _p(x, "x"), _p(xn, "xn", x.dtype)
+    pw, pb = _p(w, "w", _F32), _p(bias, "bias", _F32)
     n, cu_h = _conv_packing(x, cu_seqlens, cu_seqlens_host)
     if xn.shape != x.shape or w.dim() != 2 or w.shape[0] != x.shape[2]:
         raise ValueError("xn must match x and w must be [channels, width]")
-    desc = make_conv_desc(x, w, block=block, activation=activation, num_seqs=n)
+    plan = _conv_desc(x, w, block, activation, n)
     if y is None:
         y = torch.empty_like(x)
     if yn is None:
         yn = torch.empty_like(x)
-    _dev(y, "y", x.dtype)
-    _dev(yn, "yn", x.dtype)
-    st = lib.bdgdn_shortconv_fwd(ctypes.byref(desc), _ptr(x), _ptr(xn), _ptr(w), _ptr(bias), _ptr(cu_seqlens),
-                                 None if cu_h is None else ctypes.c_void_p(cu_h.data_ptr()), _ptr(y), _ptr(yn),
-                                 _stream(stream))
+    py, pyn = _p(y, "y", x.dtype), _p(yn, "yn", x.dtype)
+    st = lib.bdgdn_shortconv_fwd(plan[1], px, pxn, pw, pb, None if cu_seqlens is None else cu_seqlens.data_ptr(),
+                                 None if cu_h is None else cu_h.data_ptr(), py, pyn, _stream(stream))
     _check(st, "bdgdn_shortconv_fwd")
     return y, yn
 
@@ -648,7 +672,7 @@ def bdgdn_shortconv_bwd(x, xn, w, bias, dy, dyn, *, block, activation=BDGDN_ACT_
     _dev(w, "w", torch.float32)
     _dev(bias, "bias", torch.float32)
     n, cu_h = _conv_packing(x, cu_seqlens, cu_seqlens_host)
-    desc = make_conv_desc(x, w, block=block, activation=activation, num_seqs=n)
+    plan = _conv_desc(x, w, block, activation, n)
     dx = torch.empty_like(x) if dx is None else dx
     dxn = torch.empty_like(x) if dxn is None else dxn
     dw = torch.empty_like(w) if dw is None else dw
@@ -657,11 +681,11 @@ def bdgdn_shortconv_bwd(x, xn, w, bias, dy, dyn, *, block, activation=BDGDN_ACT_
     for name, t, dt in (("dx", dx, x.dtype), ("dxn", dxn, x.dtype), ("dw", dw, torch.float32),
                         ("dbias", dbias, torch.float32)):
         _dev(t, name, dt)
-    ws_bytes = bdgdn_shortconv_bwd_workspace(desc)
+    ws_bytes = _plan_bytes(plan, bdgdn_shortconv_bwd_workspace)
     if workspace is None and ws_bytes:
         workspace = torch.empty(ws_bytes, dtype=torch.uint8, device=x.device)
     ws_size = 0 if workspace is None else workspace.numel() * workspace.element_size()
-    st = lib.bdgdn_shortconv_bwd(ctypes.byref(desc), _ptr(x), _ptr(xn), _ptr(w), _ptr(bias), _ptr(dy), _ptr(dyn),
+    st = lib.bdgdn_shortconv_bwd(plan[1], _ptr(x), _ptr(xn), _ptr(w), _ptr(bias), _ptr(dy), _ptr(dyn),
                                  _ptr(cu_seqlens), None if cu_h is None else ctypes.c_void_p(cu_h.data_ptr()),
                                  _ptr(dx), _ptr(dxn), _ptr(dw), _ptr(dbias), _ptr(workspace), ws_size,
                                  _stream(stream))
