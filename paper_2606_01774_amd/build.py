@@ -17,17 +17,18 @@ INCLUDE = os.path.join(ROOT, "include")
 LIB = os.path.join(PKG, "libbdgdn.so")
 SOURCES = ["api.hip", "fwd_kernels.hip", "fwd_scan_kernels.hip", "fused_kernels.hip", "serve_kernels.hip",
            "split_kernels.hip", "conv_kernels.hip", "bwd_kernels.hip", "chunked_kernels.hip",
-           "bwd_generic.hip", "bwd_steps.hip"]
+           "bwd_generic.hip", "bwd_steps.hip", "bwd_scan.hip"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-I" + INCLUDE, "-I" + CSRC,
          # no packed-fp32 instructions in the device code
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops"]
 
 
-# Per-source extra flags.  The chunk-parallel kernels keep their MFMA accumulators in
+# Per-source extra flags.  The chunk-parallel and the backward scan kernels keep their MFMA accumulators in
 # ordinary VGPRs (the compiler's default AGPR form copies every accumulator that VALU code
 # touches in and out of the accumulation registers).
-EXTRA = {"chunked_kernels.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"]}
+EXTRA = {"chunked_kernels.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"],
+         "bwd_scan.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"]}
 
 
 def _compile(src: str, objdir: str) -> str:

@@ -110,6 +110,8 @@ size_t bwd_block_lds();
 // noisy blocks x v-heads).
 hipError_t launch_bwd(bool bf16_out, const BwdArgs &a, const BwdView *more, int n_more, int n_chains,
                       long n_block_units, long n_pair_units, hipStream_t s);
+// Its reverse scan alone (bwd_scan.hip; a.n_chains chains).
+hipError_t launch_bwd_scan(const BwdArgs &a, hipStream_t s);
 // The segment tables of a segmented backward: for segments k = 0 .. n_seg - 1 of seg_len
 // blocks of L positions, seg[k][n] = the blocks of sequences 0 .. n - 1 inside segment k and
 // segp[k][n] = their noisy blocks of two sub-blocks (n = 0 .. n_seq); lengths from cu

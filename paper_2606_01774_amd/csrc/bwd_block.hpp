@@ -364,19 +364,23 @@ template <typename Od, bool PREP> __global__ void __launch_bounds__(512, 4) bdgd
                     for (int j = 0; j < 4; ++j) d[j] = ex(Ge - sm.G[16 * tm + 4 * g4 + j]);
                     kd[tm] = scale4(op_tr(sm.K, LDH, 16 * tm, c0, lane), d);
                 }
+// U K = Gamma diag(beta) M^T (D K)
+                _Float16 *uk = a.uk + (size_t)uw * NP * DD;
+#pragma unroll
+                for (int tm = 0; tm < 2; ++tm) {
+                    // the transpose from the swapped operands, in the scan's order
+                    const float f = sm.gam[16 * tm + rr] * sm.bet[16 * tm + rr];
+                    const f32x4 u = mfma2(kd[0], kd[1], op_tr(sm.Mc, LDM, 0, 16 * tm, lane),
+                                          op_tr(sm.Mc, LDM, 16, 16 * tm, lane), z);
+                    put_uk(uk, tm, wave, lane, h4(f * u));
+                }
+                // the c term
 #pragma unroll
                 for (int tm = 0; tm < 8; ++tm) {
                     f32x4 c = apply_t(sm.K, LDH, 16 * tm, drq, z, lane);
                     c = apply_t(sm.Q, LDH, 16 * tm, sd, c, lane);
                     c = apply_t(sm.Qn, LDH, 16 * tm, aq, c, lane);
                     ct[tm * 8 * 64] = h4(apply_t(sm.Kn, LDH, 16 * tm, bq, c, lane));
-                }
-                // U K = Gamma diag(beta) M^T (D K)
-                _Float16 *uk = a.uk + (size_t)uw * NP * DD;
-#pragma unroll
-                for (int tm = 0; tm < 2; ++tm) {
-                    const f32x4 f = ld4(sm.gam + 16 * tm + 4 * g4) * ld4(sm.bet + 16 * tm + 4 * g4);
-                    put_tile(uk, DD, 16 * tm, col, h4(f * apply_t(sm.Mc, LDM, 16 * tm, kd, z, lane)), g4);
                 }
                 if (tid == 0) a.gnb[uw] = ex(Ge);
             } else {

@@ -309,6 +309,14 @@ __device__ __forceinline__ BlockRows<Od, WITH_V> load_block(const StreamPtrs &p,
 
 }  // namespace
 
+// Rows 16 tm .. of U K, columns 16 w .. 16 w + 15, into the order the scan reads as operands: 16 x 32
+// tiles (tm, w / 2), lane (g, n) holding row n, columns 4 g .. 4 g + 3 of both 16-column halves.
+// x: lane (g, n)'s four entries (a C tile of (U K)^T).
+__device__ __forceinline__ void put_uk(_Float16 *uk, int tm, int w, int lane, f16x4 x)
+{
+    *reinterpret_cast<f16x4 *>(uk + ((4 * tm + (w >> 1)) * 64 + lane) * 8 + 4 * (w & 1)) = x;
+}
+
 // q/k gradient x into *dst: stored for the first v-head of a q/k head, added for the others
 // (a workgroup runs the v-heads of a q/k head one after the other, and the same thread
 // writes the same element for each, so the sum has a fixed order; see unit_of).
@@ -920,9 +928,9 @@ __device__ __forceinline__ void clean_prep(Smem &sm, const BwdArgs &a, float gx,
         const f16x4 k0q = op_tr(Ks, LDH, 0, c0, lane), k1q = op_tr(Ks, LDH, 16, c0, lane);
 #pragma unroll
         for (int tm = 0; tm < 2; ++tm) {
-            const f32x4 u = mfma(op_row(sm.Wh, LDM, 16 * tm, 16, lane), k1q, mfma(op_row(sm.Wh, LDM, 16 * tm, 0, lane), k0q, z));
-#pragma unroll
-            for (int j = 0; j < 4; ++j) uk[(16 * tm + 4 * g4 + j) * DD + c0 + rr] = (_Float16)u[j];
+            // (U K)^T from the swapped operands: the scan's operand order
+            const f32x4 u = mfma(k1q, op_row(sm.Wh, LDM, 16 * tm, 16, lane), mfma(k0q, op_row(sm.Wh, LDM, 16 * tm, 0, lane), z));
+            put_uk(uk, tm, wave, lane, h4(u));
         }
     }
     __syncthreads();
@@ -1131,215 +1139,6 @@ __global__ void __launch_bounds__(512) bdgdn_bwd_pair_kernel(BwdArgs a)
 
 #include "bwd_small.hpp"
 
-// Phase 2: the reverse scan of the clean state gradient over the blocks of a (sequence,
-// v-head) (a chain), one workgroup of NW waves per TC = 8 NW columns (the columns are
-// independent):
-//   dh_(b-1) = gamma_n dh_b + cterm_b - K^T Z,  Z = (U K) dh_b  (32 x TC),
-// writing dh_b (the gradient at the end of block b; fp16, the precision phase 3 uses it in,
-// tile-native) over cterm_b, which only this scan reads, for phase 3, and dh0 (fp32).  The operands of block b - 2 (U K, K, cterm, gamma_n) are
-// loaded into registers while block b is computed.
-namespace {
-constexpr int LDK = NP + 8;   // f16 row stride of [*][32] tiles
-constexpr int kScanWaves = 4;   // waves per workgroup (2: 16 columns, two workgroups per CU, was slower)
-template <int TC> struct ScanSmem {
-    _Float16 UK[NP * LDH];       // U K of the block (32 x 128)
-    _Float16 dHt[TC * LDH];      // dh_b transposed: the tile's TC columns x 128 rows
-    _Float16 Kr[2][NP * LDH];    // K (32 x 128, row-major; its transpose is read by transpose loads), two buffers
-    _Float16 Zt[TC * LDK];       // Z transposed: TC columns x 32 positions
-};
-}  // namespace
-
-template <int NW>
-__global__ void __launch_bounds__(64 * NW) bdgdn_bwd_scan_kernel(BwdArgs a)
-{
-    constexpr int TC = 8 * NW;           // columns per workgroup
-    constexpr int NT = DD / TC;          // column tiles per chain
-    constexpr int RT = DD / (16 * NW);   // 16-row tiles of dh per wave
-    constexpr int CT = TC / 16;          // 16-column tiles
-    constexpr int NC = 8 / NW;           // 16-byte chunks of a 32 x 128 operand per thread
-    __shared__ __align__(16) ScanSmem<TC> sm;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, g4 = lane >> 4, rr = lane & 15;
-    // the NT column tiles of a chain on one XCD (workgroups are dealt to the 8 XCDs in turn),
-    // so that they read its U K and K rows through one L2
-    const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
-    const int chain = (slot / NT) * 8 + xcd, v0 = TC * (slot % NT);
-    if (chain >= a.n_chains) return;
-    const int n = chain / a.h_v, h = chain % a.h_v, hq = h / (a.h_v / a.h_qk);
-    long r0, r1;
-    if (a.cu) {
-        r0 = a.cu[n];
-        r1 = a.cu[n + 1];
-    } else {
-        r0 = (long)n * a.T;
-        r1 = r0 + a.T;
-    }
-    const int nb = (int)((r1 - r0 + a.L - 1) / a.L);
-    // the blocks walked, blo .. bhi - 1, and the workspace unit of block b, gb0 + b: all the
-    // chain's blocks by global index (documents start on block boundaries), or those of one
-    // time segment numbered from seg[n]; the walk starts from dht where the chain ends in it,
-    // else from the gradient the next segment left in carry, and ends in dh0 at the chain's
-    // start, else in carry
-    int blo = 0, bhi = nb;
-    long gb0 = a.cu ? r0 / a.L : (long)n * a.nblk;
-    bool from_dht = true, to_dh0 = true;
-    if (a.seg) {
-        blo = a.blk0;
-        bhi = nb < a.blk0 + a.seg_len ? nb : a.blk0 + a.seg_len;
-        // no blocks of this chain in the segment: nothing to do, but for an empty chain,
-        // whose dh0 is dht, in the first segment
-        if (bhi <= blo && !(nb == 0 && a.blk0 == 0)) return;
-        gb0 = a.seg[n] - blo;
-        from_dht = nb <= a.blk0 + a.seg_len;
-        to_dh0 = a.blk0 == 0;
-    }
-    const size_t SS = (size_t)DD * DD;
-    const long qks = (long)a.h_qk * DD;
-    // dh tiles: wave w holds rows (128 / NW) w .. + 128 / NW - 1 (RT row tiles) of the TC columns
-    const int rw = (DD / NW) * wave;
-    float dh[RT][CT][4];
-    const float *dht = a.dht ? a.dht + ((size_t)n * a.h_v + h) * SS : nullptr;
-    float *carry = a.seg ? a.carry + ((size_t)n * a.h_v + h) * SS : nullptr;
-    const float sg = a.range[0];
-#pragma unroll
-    for (int tl = 0; tl < RT; ++tl)
-#pragma unroll
-        for (int tn = 0; tn < CT; ++tn)
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const int e = (rw + 16 * tl + 4 * g4 + j) * DD + v0 + 16 * tn + rr;
-                // the carry holds dh as the walk keeps it (times sigma)
-                dh[tl][tn][j] = !from_dht ? carry[e] : (dht ? dht[e] * sg : 0.f);
-            }
-    // wait for these loads here, once: left pending into the loop, they would make every
-    // step wait for all outstanding loads (the prefetch of the next blocks included)
-#pragma unroll
-    for (int tl = 0; tl < RT; ++tl)
-#pragma unroll
-        for (int tn = 0; tn < CT; ++tn)
-#pragma unroll
-            for (int j = 0; j < 4; ++j) asm volatile("" : "+v"(dh[tl][tn][j]));
-    // staging map of the 32 x 128 operands: NC consecutive 16-byte chunks of one row per thread
-    const int sr = (tid * NC) >> 4, sc = ((tid * NC) & 15) * 8;
-    // one block's operands in registers; three sets rotate so that the loads for blocks
-    // b - 1 and b - 2 are in flight while block b is computed (no register copy waits on them)
-    struct Ops {
-        f16x8 uk[NC];
-        bf16x8 k[NC];
-        f16x4 cs[RT][CT];
-        float gn;
-    };
-    auto fetch = [&](int b, Ops &o) {
-        const long p0 = r0 + (long)b * a.L;
-        const int nvalid = (int)(r1 - p0 < a.L ? r1 - p0 : a.L);
-        const size_t unit = (size_t)(gb0 + b) * a.h_v + h;
-        const f16x8 *u = reinterpret_cast<const f16x8 *>(a.uk + unit * NP * DD + sr * DD + sc);
-#pragma unroll
-        for (int i = 0; i < NC; ++i) o.uk[i] = u[i];
-        if (sr < nvalid) {
-            const bf16x8 *k = reinterpret_cast<const bf16x8 *>(static_cast<const __bf16 *>(a.k) + (p0 + sr) * qks +
-                                                               hq * DD + sc);
-#pragma unroll
-            for (int i = 0; i < NC; ++i) o.k[i] = k[i];
-        } else {
-#pragma unroll
-            for (int i = 0; i < NC; ++i)
-#pragma unroll
-                for (int j = 0; j < 8; ++j) o.k[i][j] = (__bf16)0.f;
-        }
-        // cterm tiles (rows rw / 16 + tl, columns v0 / 16 + tn), lane-major like the dh tiles
-        const f16x4 *c = reinterpret_cast<const f16x4 *>(a.cterm + unit * SS) + lane;
-#pragma unroll
-        for (int tl = 0; tl < RT; ++tl)
-#pragma unroll
-            for (int tn = 0; tn < CT; ++tn) o.cs[tl][tn] = c[((rw / 16 + tl) * 8 + v0 / 16 + tn) * 64];
-        // a vector load (the index made lane-opaque): a scalar load would be counted with the
-        // LDS operations, and the wait before the next barrier would wait for it
-        int z;
-        asm volatile("v_mov_b32 %0, 0" : "=v"(z));
-        o.gn = a.gnb[unit + z];
-    };
-    const f32x4 z = {0.f, 0.f, 0.f, 0.f};
-    auto step = [&](int b, const Ops &cur, Ops &nxt) {
-        const int buf = b & 1;
-        // dh_b goes to block b's cterm slot (tile-native, fp16), which this lane read two
-        // steps earlier: the store is issued after that value's use below
-        f16x4 *dhb = reinterpret_cast<f16x4 *>(a.dh + ((size_t)(gb0 + b) * a.h_v + h) * SS) + lane;
-        f16x4 hv[RT][CT];
-        // stage dh_b^T, U K, K^T of block b; every use of cur comes before the loads of block
-        // b - 2 are issued, so that no wait for cur can also wait for those
-#pragma unroll
-        for (int tl = 0; tl < RT; ++tl)
-#pragma unroll
-            for (int tn = 0; tn < CT; ++tn) {
-                const int r = rw + 16 * tl + 4 * g4, c = 16 * tn + rr;
-                hv[tl][tn] = f16x4{(_Float16)dh[tl][tn][0], (_Float16)dh[tl][tn][1], (_Float16)dh[tl][tn][2],
-                                   (_Float16)dh[tl][tn][3]};
-                st4(sm.dHt + c * LDH + r, dh[tl][tn][0], dh[tl][tn][1], dh[tl][tn][2], dh[tl][tn][3]);
-            }
-#pragma unroll
-        for (int i = 0; i < NC; ++i) {
-            *reinterpret_cast<f16x8 *>(sm.UK + sr * LDH + sc + 8 * i) = cur.uk[i];
-            f16x8 kh;
-#pragma unroll
-            for (int j = 0; j < 8; ++j) kh[j] = (_Float16)(float)cur.k[i][j];
-            *reinterpret_cast<f16x8 *>(sm.Kr[buf] + sr * LDH + sc + 8 * i) = kh;
-        }
-        // dh_b is in LDS now: keep gamma_n dh_b + cterm_b in its registers
-#pragma unroll
-        for (int tl = 0; tl < RT; ++tl)
-#pragma unroll
-            for (int tn = 0; tn < CT; ++tn)
-#pragma unroll
-                for (int j = 0; j < 4; ++j) dh[tl][tn][j] = cur.gn * dh[tl][tn][j] + (float)cur.cs[tl][tn][j];
-#pragma unroll
-        for (int tl = 0; tl < RT; ++tl)
-#pragma unroll
-            for (int tn = 0; tn < CT; ++tn) dhb[((rw / 16 + tl) * 8 + v0 / 16 + tn) * 64] = hv[tl][tn];
-        if (b - 2 >= blo) fetch(b - 2, nxt);
-        __syncthreads();
-        {   // Z = (U K) dh_b: one 16 x 16 tile per wave (2 CT tiles over NW = 2 CT waves), stored transposed
-            const int m0 = 16 * (wave / CT), n0 = 16 * (wave % CT);
-            const f32x4 c = tile_mma<_Float16, DD>(z, sm.UK + m0 * LDH, LDH, sm.dHt + n0 * LDH, LDH, lane);
-            st4(sm.Zt + (n0 + rr) * LDK + m0 + 4 * g4, c[0], c[1], c[2], c[3]);
-        }
-        __syncthreads();
-#pragma unroll
-        for (int tl = 0; tl < RT; ++tl)
-#pragma unroll
-            for (int tn = 0; tn < CT; ++tn) {
-                // K^T Z: the A operand K^T by transpose loads of the row-major K, positions in two
-                // 16-halves (the same k order as the Zt operand's)
-                const int m0 = rw + 16 * tl;
-                const f32x4 c = mfma(op_tr(sm.Kr[buf], LDH, 16, m0, lane), op_row(sm.Zt, LDK, 16 * tn, 16, lane),
-                                     mfma(op_tr(sm.Kr[buf], LDH, 0, m0, lane), op_row(sm.Zt, LDK, 16 * tn, 0, lane), z));
-#pragma unroll
-                for (int j = 0; j < 4; ++j) dh[tl][tn][j] -= c[j];
-            }
-    };
-    // three sets: block b's operands were loaded two steps earlier
-    Ops o0, o1, o2;
-    if (bhi - blo > 0) fetch(bhi - 1, o0);
-    if (bhi - blo > 1) fetch(bhi - 2, o1);
-    for (int b = bhi - 1; b >= blo; b -= 3) {
-        step(b, o0, o2);
-        if (b == blo) break;
-        step(b - 1, o1, o0);
-        if (b == blo + 1) break;
-        step(b - 2, o2, o1);
-    }
-    float *d0 = !to_dh0 ? carry : (a.dh0 ? a.dh0 + ((size_t)n * a.h_v + h) * SS : nullptr);
-    if (d0) {
-        const float f = to_dh0 ? a.range[1] : 1.f;
-#pragma unroll
-        for (int tl = 0; tl < RT; ++tl)
-#pragma unroll
-            for (int tn = 0; tn < CT; ++tn)
-#pragma unroll
-                for (int j = 0; j < 4; ++j)
-                    d0[(rw + 16 * tl + 4 * g4 + j) * DD + v0 + 16 * tn + rr] = dh[tl][tn][j] * f;
-    }
-}
-
 // The range of the upstream gradients (dO, dO~ of every view, dht): each block's max |x| over
 // its grid-stride share of every array into part[blockIdx.x].  With Od = bf16 the output
 // gradients are bf16 (dht is always fp32).
@@ -1537,10 +1336,7 @@ hipError_t launch_bwd(bool bf16_out, const BwdArgs &a, const BwdView *more, int 
                 if ((e = hipGetLastError()) != hipSuccess) return e;
             }
         }
-        constexpr int NT = DD / (8 * kScanWaves);   // column tiles per chain
-        hipLaunchKernelGGL(bdgdn_bwd_scan_kernel<kScanWaves>, dim3((NT * n_chains + 8 * NT - 1) / (8 * NT) * 8 * NT),
-                           dim3(64 * kScanWaves), 0, s, a);
-        if ((e = hipGetLastError()) != hipSuccess) return e;
+        if ((e = launch_bwd_scan(a, s)) != hipSuccess) return e;
         if (groups > 0) {
             hipLaunchKernelGGL(a.nl > 0 ? clean_small : clean, dim3((unsigned)groups), dim3(512),
                                sizeof(CleanSmem), s, a2);

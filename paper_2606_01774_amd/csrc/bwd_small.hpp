@@ -300,8 +300,11 @@ template <typename Od> __global__ void __launch_bounds__(512) bdgdn_bwd_small_ke
             _Float16 *uk = a.uk + (size_t)uw * NP * DD;
 #pragma unroll
             for (int tm = 0; tm < 2; ++tm) {
-                const f32x4 f = ld4(sm.gam + 16 * tm + 4 * g4) * ld4(sm.bet + 16 * tm + 4 * g4);
-                put_tile(uk, DD, 16 * tm, col, h4(f * apply_t(sm.Mc, LDM, 16 * tm, kd, z, lane)), g4);
+                // the transpose from the swapped operands, in the scan's order
+                const float f = sm.gam[16 * tm + rr] * sm.bet[16 * tm + rr];
+                const f32x4 u = mfma2(kd[0], kd[1], op_tr(sm.Mc, LDM, 0, 16 * tm, lane),
+                                      op_tr(sm.Mc, LDM, 16, 16 * tm, lane), z);
+                put_uk(uk, tm, wave, lane, h4(f * u));
             }
             if (tid == 0) a.gnb[uw] = ex(Ge);
         }
