@@ -24,7 +24,8 @@ struct BwdArgs {
     _Float16 *cterm;                         // [global block][h_v][64 tiles][64 lanes][4]: the part of dh_(b-1)
                                              // that does not depend on dh_b (noisy seed gradient
                                              // + clean terms), fp16 like dh
-    _Float16 *uk;                            // [global block][h_v][32][128]: U K of each clean block
+    _Float16 *uk;                            // [global block][h_v][32 x 128]: U K of each clean block, in
+                                             // the scan's operand order (put_uk)
     float *gnb;                              // [global block][h_v]: gamma_n of each clean block
     _Float16 *dh;                            // [global block][h_v][64 tiles][64 lanes][4]: gradient at
                                              // block ends (fp16, tile-native like cterm; may be cterm
@@ -103,7 +104,6 @@ hipError_t launch_bwd_generic(bool f32_in, bool f32_out, const GenBwdCall &c, hi
 constexpr size_t kStepsMaxBytes = (size_t)2 << 30;
 size_t bwd_steps_workspace(long total_blocks, int h_v, int dk, int dv);
 hipError_t launch_bwd_steps(bool f32_in, bool f32_out, const GenBwdCall &c, hipStream_t s);
-size_t bwd_block_lds();
 // The backward of a's two streams, plus n_more further noisy views seeded from the same clean
 // states (their seed gradients summed into the clean state gradient).  a.L is the clean
 // block; with n_pair_units > 0 every noisy block spans two clean blocks (n_pair_units =

@@ -364,7 +364,7 @@ template <typename Od, bool PREP> __global__ void __launch_bounds__(512, 4) bdgd
                     for (int j = 0; j < 4; ++j) d[j] = ex(Ge - sm.G[16 * tm + 4 * g4 + j]);
                     kd[tm] = scale4(op_tr(sm.K, LDH, 16 * tm, c0, lane), d);
                 }
-// U K = Gamma diag(beta) M^T (D K)
+                // U K = Gamma diag(beta) M^T (D K)
                 _Float16 *uk = a.uk + (size_t)uw * NP * DD;
 #pragma unroll
                 for (int tm = 0; tm < 2; ++tm) {
