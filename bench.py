@@ -685,7 +685,8 @@ def main():
         per_step = {}
         block_form = ("bdgdn_k2_scan_states_kernel (seed states) + bdgdn_bwd_noisy_kernel + "
                       "bdgdn_bwd_scan_kernel + bdgdn_bwd_clean_kernel")
-        paths = {"tiny_f32": ("bdgdn_bwd_gen_ckpt_kernel + bdgdn_bwd_gen_walk_kernel (fp32, per step)", 1, 3, 1),
+        paths = {"tiny_f32": ("bdgdn_bwd_steps_states_kernel + bdgdn_bwd_steps_block_kernel + "
+                              "bdgdn_bwd_steps_reverse_kernel (fp32, per step)", 1, 3, 1),
                  "gva_16k": ("bdgdn_k2_scan_states_kernel (seed states per 32-position sub-block) + "
                         "bdgdn_bwd_pair_kernel + bdgdn_bwd_scan_kernel + bdgdn_bwd_clean_kernel", 3, 10, 3),
                  "varlen_128k": (block_form, 3, 10, 3)}

@@ -23,14 +23,13 @@
 // seed), for half a also that of k~b . (ea Bb S0^T).
 //
 // One workgroup per CU (157 KB of LDS), bound by what it waits for: 30 us a unit, of which
-// its 340 KB of HBM traffic are 17 at a large copy's rate, the rest barriers (9.5 k clocks to
-// the end of the solves, 10 k for the columns' products and the clean preparation, 10 k for the
-// tiles over the columns).  At 2 x 16384 tokens, 32 v-heads over 16 q/k heads, blocks of 64 (16384
-// units): 3300 -> 1976 us against one workgroup of eight waves forming S~1, S~2 and their
-// gradients.  Loading the next unit's inputs during the last phases from a persistent grid took
-// 2040 us (they don't fit beside the last phases: nine registers spilled, and waves stall at
-// the issue of loads); the gate terms of the last positions summed per lane instead of per
-// row saved 100 us.
+// its 430 KB of HBM traffic are 22 at a large copy's rate, which do not overlap the barriers
+// (9.5 k clocks to the end of the solves, 10 k for the columns' products and the clean
+// preparation, 10 k for the tiles over the columns).  At 2 x 16384 tokens, 32 v-heads over 16
+// q/k heads, blocks of 64 (16384 units): 3300 -> 1976 us against one workgroup of eight waves
+// forming S~1, S~2 and their gradients.  Loading the next unit's inputs during the last phases
+// from a persistent grid took 2040 us (they don't fit beside the last phases: nine registers
+// spilled, and waves stall at the issue of loads).
 
 struct PairSmem {
     _Float16 Qn[2 * NP * LDH], Kn[2 * NP * LDH];   // rows 0 .. 31 half a, 32 .. 63 half b
