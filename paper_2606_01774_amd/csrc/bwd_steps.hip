@@ -15,14 +15,15 @@
 //   3. reverse: the gradient dh of the state at every block's end (one wave per 4 columns),
 //      stored over the seed gradients it has consumed;
 //   4. clean blocks in parallel from the state at their start and dh.
-// A block (2, 4) is three walks over its positions: forwards for u (and the clean dq),
-// backwards for w, dv, dbeta and the first part of dk, forwards again for the second part of
-// dk.  The gate gradient needs no further state: with dg_i = <dS^_i, alpha S_(i-1)> (dS^ the
-// gradient of the decayed state) one step gives
-//     dg_(i-1) = dg_i + do_(i-1) . o_(i-1) - dv_(i-1) . v_(i-1),
-// started from <dh, S_n> at the block's end and again from <dS, S> at its middle (every
-// rounding of a state between start and use stays in the sum), with do . o = q . dq and
-// dv . v = beta dbeta - k . (second part of dk), summed in 64 bits.
+// A block (2, 4) is two walks over its positions: forwards for u (and the clean dq), then
+// backwards for w, dv, dbeta, dk and dg.  The second needs the state before each position, which
+// a step of the first cannot be run back to (it would divide by alpha): four positions at a time
+// it is rebuilt from the block's seed or the state kept at the block's middle by the steps' stored
+// u, S' = alpha S + beta k u^T, which sums over nothing.  The gate gradient is the inner product
+// dg = <dS^, alpha S> (dS^ the gradient of the decayed state), every term of which carries alpha: a
+// running sum dg_(i-1) = dg_i + do.o - dv.v over the block, though it needs no states, leaves the
+// rounding of terms of order one in a result of order alpha (7e-4 of it at g = -8, 40 times it at
+// g = -20).
 //
 // Layout: 16 lanes of a DPP row share a column's rows (d_k / 16 consecutive rows each), so a
 // column sum over rows is four DPP adds; the four DPP rows hold different columns.  Row sums
@@ -106,13 +107,14 @@ __device__ __forceinline__ float rows4_sum(float x)
     return swap16_sum(x, x);
 }
 // x[m] (m < NR) summed over the four DPP rows; lane (cg, rl) ends with the sums of rows
-// cg NR / 4 .. cg NR / 4 + NR / 4 - 1 of its NR rows in x[0 .. NR / 4 - 1]
-template <int NR> __device__ __forceinline__ void rows4_scatter(float (&x)[NR])
+// cg NR / 4 .. cg NR / 4 + NR / 4 - 1 of its NR rows in y
+template <int NR> __device__ __forceinline__ void rows4_scatter(const float (&x)[NR], float (&y)[NR / 4])
 {
+    float z[NR / 2];
 #pragma unroll
-    for (int m = 0; m < NR / 2; ++m) x[m] = swap32_sum(x[m], x[m + NR / 2]);
+    for (int m = 0; m < NR / 2; ++m) z[m] = swap32_sum(x[m], x[m + NR / 2]);
 #pragma unroll
-    for (int m = 0; m < NR / 4; ++m) x[m] = swap16_sum(x[m], x[m + NR / 4]);
+    for (int m = 0; m < NR / 4; ++m) y[m] = swap16_sum(z[m], z[m + NR / 4]);
 }
 
 // A chain's first row, length and the workspace unit of its first block.
@@ -228,7 +230,7 @@ __global__ void __launch_bounds__(64) bdgdn_bwd_steps_states_kernel(StepArgs a)
             }
             const float bu = beta * (to_f(b.v[j]) - alpha * row16_sum(x));
 #pragma unroll
-            for (int m = 0; m < NR; ++m) S[m] = fmaf(k[m], bu, alpha * S[m]);
+            for (int m = 0; m < NR; ++m) S[m] = fmaf(alpha, S[m], k[m] * bu);   // the rounding of the product is the small one
         }
     };
     Buf b0, b1;
@@ -369,27 +371,23 @@ template <typename In, typename Out, int DK, int DV> struct BlockLds {
     Out *d;          // [L][DV]
     float *u, *w;    // [L][DV]: u holds v until u replaces it
     float *red;      // [W][kSpan][DK]
-    float *pa, *pb, *pc;   // [L][W]: q . dq, w . u, k . (second part of dk)
+    float *pb, *pg;  // [L][W]: w . u, <dS^, alpha S>
     float *al, *be;  // [kMaxL]
-    float *tot, *mid;   // [W]: <dh, S_n> and <dS, S> at the block's middle
     static size_t bytes(int L)
     {
-        return (size_t)L * (2 * DK * sizeof(In) + DV * sizeof(Out) + 2 * DV * 4 + 3 * W * 4) + W * kSpan * DK * 4 +
-               2 * kMaxL * 4 + 2 * W * 4;
+        return (size_t)L * (2 * DK * sizeof(In) + DV * sizeof(Out) + 2 * DV * 4 + 2 * W * 4) + W * kSpan * DK * 4 +
+               2 * kMaxL * 4;
     }
     __device__ BlockLds(unsigned char *p, int L)
     {
         u = reinterpret_cast<float *>(p);
         w = u + L * DV;
         red = w + L * DV;
-        pa = red + W * kSpan * DK;
-        pb = pa + L * W;
-        pc = pb + L * W;
-        al = pc + L * W;
+        pb = red + W * kSpan * DK;
+        pg = pb + L * W;
+        al = pg + L * W;
         be = al + kMaxL;
-        tot = be + kMaxL;
-        mid = tot + W;
-        q = reinterpret_cast<In *>(mid + W);
+        q = reinterpret_cast<In *>(be + kMaxL);
         k = q + L * DK;
         d = reinterpret_cast<Out *>(k + L * DK);
     }
@@ -402,7 +400,7 @@ template <typename In, typename Out, int DK, int DV> struct Block {
     Lds s;
     int tid, lane, wave, rl, col;   // col: this lane's first of 4 columns
     int n;                          // positions of the block
-    float S[NR][4];
+    f32x4 S[NR];
 
     __device__ Block(const StepArgs &a_, unsigned char *smem) : a(a_), s(smem, a_.L)
     {
@@ -421,7 +419,7 @@ template <typename In, typename Out, int DK, int DV> struct Block {
             *reinterpret_cast<Vec<T, E> *>(dst + r * D + c) = ldv<T, E>(src + r * stride + c);
         }
     }
-    __device__ __forceinline__ void load_state(float (&x)[NR][4], const float *p) const   // column-major
+    __device__ __forceinline__ void load_state(f32x4 (&x)[NR], const float *p) const   // column-major
     {
 #pragma unroll
         for (int c = 0; c < 4; ++c)
@@ -445,12 +443,13 @@ template <typename In, typename Out, int DK, int DV> struct Block {
         for (int c = 0; c < 4; ++c) x[c] = to_f(y.v[c]);
     }
     // this wave's sums over its columns of the row vector x of position i0 + slot
-    __device__ __forceinline__ void put_rows(float (&x)[NR], int slot)
+    __device__ __forceinline__ void put_rows(const float (&x)[NR], int slot)
     {
-        rows4_scatter<NR>(x);
+        float y[NR / 4];
+        rows4_scatter<NR>(x, y);
         float *p = s.red + (wave * kSpan + slot) * DK + rl * NR + (lane >> 4) * (NR / 4);
 #pragma unroll
-        for (int m = 0; m < NR / 4; ++m) p[m] = x[m];
+        for (int m = 0; m < NR / 4; ++m) p[m] = y[m];
     }
     // the waves' row sums of positions i0 .. i0 + cnt - 1 to dst (rows of stride ld): stored,
     // or added to what this same thread stored before
@@ -468,7 +467,14 @@ template <typename In, typename Out, int DK, int DV> struct Block {
         __syncthreads();
     }
 
-    __device__ __forceinline__ void store_state(float *p, const float (&x)[NR][4]) const
+    __device__ __forceinline__ void copy(f32x4 (&x)[NR], const f32x4 (&y)[NR]) const
+    {
+#pragma unroll
+        for (int m = 0; m < NR; ++m)
+#pragma unroll
+            for (int c = 0; c < 4; ++c) x[m][c] = y[m][c];
+    }
+    __device__ __forceinline__ void store_state(float *p, const f32x4 (&x)[NR]) const
     {
 #pragma unroll
         for (int c = 0; c < 4; ++c)
@@ -476,15 +482,22 @@ template <typename In, typename Out, int DK, int DV> struct Block {
             for (int m = 0; m < NR; m += 4)
                 st4(p + (long)(col + c) * DK + rl * NR + m, x[m][c], x[m + 1][c], x[m + 2][c], x[m + 3][c]);
     }
-    // <x, y> over this wave's columns, in every lane
-    __device__ __forceinline__ float inner(const float (&x)[NR][4], const float (&y)[NR][4]) const
+    // X, the state before position i, taken on to that before position end by the stored u
+    __device__ __forceinline__ void advance(f32x4 (&X)[NR], int i, int end) const
     {
-        float e = 0.f;
+#pragma unroll 1
+        for (; i < end; ++i) {
+            float k[NR], u[4];
+            load_k(k, s.k, i);
+            load_c(u, s.u, i);
+            const float alpha = s.al[i], beta = s.be[i];
 #pragma unroll
-        for (int m = 0; m < NR; ++m)
+            for (int c = 0; c < 4; ++c) {
+                const float bu = beta * u[c];
 #pragma unroll
-            for (int c = 0; c < 4; ++c) e = fmaf(x[m][c], y[m][c], e);
-        return rows4_sum(row16_sum(e));
+                for (int m = 0; m < NR; ++m) X[m][c] = fmaf(alpha, X[m][c], k[m] * bu);
+            }
+        }
     }
 
     // The block of stream st (clean, or a noisy view) for v-head h: rows from row p0; seed: the
@@ -493,9 +506,9 @@ template <typename In, typename Out, int DK, int DV> struct Block {
     // seed (out).  add: dq, dk add to an earlier v-head's.
     template <bool CLEAN>
     __device__ void run(const StepStream &st, long p0, int h, int hq, const float *seed, float *spare,
-                        float (&dS)[NR][4], bool add)
+                        f32x4 (&dS)[NR], bool add)
     {
-        const int half = n / 2 / kSpan * kSpan;   // 0: a short block, no restart
+        const int half = n / 2 / kSpan * kSpan;   // 0: a short block, no middle state
         const long qks = (long)a.h_qk * DK, vs = (long)a.h_v * DV;
         const long qo = (p0 * a.h_qk + hq) * DK, vo = (p0 * a.h_v + h) * DV, go = p0 * a.h_v + h;
         stage<In, DK>(s.q, static_cast<const In *>(st.q) + qo, qks);
@@ -538,10 +551,7 @@ template <typename In, typename Out, int DK, int DV> struct Block {
             }
             if constexpr (CLEAN) flush(dq, qks, i0, cnt, add);
         }
-        if constexpr (CLEAN) {
-            const float e = inner(dS, S);   // <dh, S_n>
-            if (lane == 0) s.tot[wave] = e;
-        } else {
+        if constexpr (!CLEAN) {
             // every position reads the end state: dq_i = s S~ do_i, dS~ = s sum q_i do_i^T
 #pragma unroll
             for (int m = 0; m < NR; ++m)
@@ -556,143 +566,90 @@ template <typename In, typename Out, int DK, int DV> struct Block {
                 flush(dq, qks, i0, cnt, add);
             }
         }
-        // backwards: w, dbeta, the first part of dk
+        // backwards: w, dbeta, dk, dg; S: the state before the span, from that before position from
+        int from = half;
+        load_state(S, half > 0 ? spare : seed);   // spare: written by this lane
         for (int i0 = (n - 1) / kSpan * kSpan; i0 >= 0; i0 -= kSpan) {
             const int cnt = n - i0 < kSpan ? n - i0 : kSpan;
+            if (i0 < from) {
+                from = 0;
+                load_state(S, seed);
+            }
+            f32x4 X[NR];   // the state before the span, then before each of its positions
+            copy(X, S);
+            advance(X, from, i0);
+            f32x4 B[NR];
+            copy(B, X);
             for (int j = cnt - 1; j >= 0; --j) {
                 const int i = i0 + j;
+                advance(X, i0, i);
                 if constexpr (CLEAN) add_outer(dS, i);
-                float k[NR], u[4], w[4], e[NR], b = 0.f;
+                float k[NR], u[4], w[4], e[NR], gs[4] = {0.f, 0.f, 0.f, 0.f}, b = 0.f;
                 load_k(k, s.k, i);
                 load_c(u, s.u, i);
                 const float alpha = s.al[i], beta = s.be[i];
 #pragma unroll
-                for (int m = 0; m < NR; ++m) e[m] = 0.f;
-#pragma unroll
                 for (int c = 0; c < 4; ++c) {
                     float x = 0.f;
 #pragma unroll
-                    for (int m = 0; m < NR; ++m) {
-                        x = fmaf(k[m], dS[m][c], x);
-                        e[m] = fmaf(dS[m][c], u[c], e[m]);
-                    }
+                    for (int m = 0; m < NR; ++m) x = fmaf(k[m], dS[m][c], x);
                     w[c] = row16_sum(x);
                     b = fmaf(w[c], u[c], b);
-                    const float bw = beta * w[c];
-#pragma unroll
-                    for (int m = 0; m < NR; ++m) dS[m][c] = alpha * fmaf(-k[m], bw, dS[m][c]);
                 }
-                b = rows4_sum(b);
-#pragma unroll
-                for (int m = 0; m < NR; ++m) e[m] *= beta;
-                if (rl == 0) st4(s.w + i * DV + col, w[0], w[1], w[2], w[3]);
-                if (lane == 0) s.pb[i * W + wave] = b;
-                put_rows(e, j);
-            }
-            flush(dk, qks, i0, cnt, add);
-            if (i0 > 0 && i0 == half) {
-                load_state(S, spare);   // written by this lane
-                const float e = inner(dS, S);
-                if (lane == 0) s.mid[wave] = e;
-            }
-        }
-        // forwards again: the second part of dk, -alpha beta S w
-        load_state(S, seed);
-        for (int i0 = 0; i0 < n; i0 += kSpan) {
-            const int cnt = n - i0 < kSpan ? n - i0 : kSpan;
-            for (int j = 0; j < cnt; ++j) {
-                const int i = i0 + j;
-                float k[NR], u[4], w[4], e[NR], b = 0.f;
-                load_k(k, s.k, i);
-                load_c(u, s.u, i);
-                load_c(w, s.w, i);
-                const float alpha = s.al[i], beta = s.be[i], f = -alpha * beta;
 #pragma unroll
                 for (int m = 0; m < NR; ++m) {
-                    float x = 0.f;
+                    float t[4];
 #pragma unroll
                     for (int c = 0; c < 4; ++c) {
-                        x = fmaf(S[m][c], w[c], x);
-                        S[m][c] = fmaf(alpha, S[m][c], k[m] * (beta * u[c]));
+                        const float sh = alpha * X[m][c], d = fmaf(-k[m], beta * w[c], dS[m][c]);
+                        t[c] = fmaf(dS[m][c], u[c], -sh * w[c]);
+                        gs[c] = fmaf(d, sh, gs[c]);
+                        dS[m][c] = alpha * d;
                     }
-                    e[m] = f * x;
-                    b = fmaf(k[m], e[m], b);
+                    e[m] = beta * ((t[0] + t[1]) + (t[2] + t[3]));
                 }
-                b = rows4_sum(row16_sum(b));
-                if (lane == 0) s.pc[i * W + wave] = b;
+                // both sums over the wave's columns: gg ends in the lower, b in the upper 32 lanes
+                float gg = row16_sum((gs[0] + gs[1]) + (gs[2] + gs[3]));
+                gg = swap32_sum(gg, b);
+                gg = swap16_sum(gg, gg);
+                if (rl == 0) st4(s.w + i * DV + col, w[0], w[1], w[2], w[3]);
+                if ((lane & 31) == 0) (lane ? s.pb : s.pg)[i * W + wave] = gg;
                 put_rows(e, j);
+                copy(X, B);
             }
-            flush(dk, qks, i0, cnt, true);
+            flush(dk, qks, i0, cnt, add);
         }
-        // dv = beta w; dbeta; dg by the reverse sum of q . dq (clean) - dv . v
+        // dv = beta w; dbeta and dg from the waves' sums
         for (int e = tid; e < n * (DV / 4); e += NT) {
             const int r = e / (DV / 4), c = e % (DV / 4) * 4;
             const f32x4 x = *reinterpret_cast<const f32x4 *>(s.w + r * DV + c);
             const float b = s.be[r];
             st4(st.dv + vo + r * vs + c, b * x[0], b * x[1], b * x[2], b * x[3]);
         }
-        if (wave == 0) {
-            // the gate gradient is a difference of sums over the block: taken in 64 bits
-            float b = 0.f;
-            double qa = 0., e = 0., end = 0.;
-            if (lane < n) {
+        if (tid < n) {
+            float b = 0.f, x = 0.f;
 #pragma unroll
-                for (int v = 0; v < W; ++v) {
-                    qa += s.pa[lane * W + v];
-                    b += s.pb[lane * W + v];
-                    e += s.pc[lane * W + v];
-                }
+            for (int v = 0; v < W; ++v) {
+                b += s.pb[tid * W + v];
+                x += s.pg[tid * W + v];
             }
-            if constexpr (CLEAN) {
-#pragma unroll
-                for (int v = 0; v < W; ++v) end += s.tot[v];
-            } else {
-                end = qa;
-#pragma unroll
-                for (int o = 1; o < 64; o <<= 1) end += __shfl_xor(end, o);
-                qa = 0.;
-            }
-            double x = lane < n ? qa - (double)s.be[lane] * b + e : 0., start = 0.;
-            if (half > 0) {
-#pragma unroll
-                for (int v = 0; v < W; ++v) start += s.mid[v];
-            }
-#pragma unroll
-            for (int o = 1; o < 64; o <<= 1) {
-                const double y = __shfl_down(x, o);
-                if (lane + o < 64) x += y;
-            }
-            const double later = __shfl(x, half);   // the terms from the middle on
-            if (lane < half)
-                x += start - later;
-            else
-                x += end;
-            if (lane < n) {
-                st.db[go + (long)lane * a.h_v] = b;
-                st.dg[go + (long)lane * a.h_v] = (float)x;
-            }
+            st.db[go + (long)tid * a.h_v] = b;
+            st.dg[go + (long)tid * a.h_v] = x;
         }
         __syncthreads();   // LDS is free for the next v-head or view
     }
-    // dq of position i from the state in S, into exchange slot j; q . dq into pa
+    // dq of position i from the state in S, into exchange slot j
     __device__ __forceinline__ void read_out(int i, int j)
     {
-        float q[NR], d[4], p[NR], b = 0.f;
-        load_k(q, s.q, i);
+        float d[4], p[NR];
         load_c(d, s.d, i);
 #pragma unroll
         for (int m = 0; m < NR; ++m) {
-            float x = 0.f;
-#pragma unroll
-            for (int c = 0; c < 4; ++c) x = fmaf(S[m][c], d[c], x);
-            p[m] = a.scale * x;
-            b = fmaf(q[m], p[m], b);
+            p[m] = a.scale * (fmaf(S[m][0], d[0], S[m][1] * d[1]) + fmaf(S[m][2], d[2], S[m][3] * d[3]));
         }
-        b = rows4_sum(row16_sum(b));
-        if (lane == 0) s.pa[i * W + wave] = b;
         put_rows(p, j);
     }
-    __device__ __forceinline__ void add_outer(float (&dS)[NR][4], int i)
+    __device__ __forceinline__ void add_outer(f32x4 (&dS)[NR], int i)
     {
         float q[NR], d[4];
         load_k(q, s.q, i);
@@ -748,12 +705,12 @@ __global__ void __launch_bounds__(4 * DV) bdgdn_bwd_steps_block_kernel(StepArgs 
     for (int vi = 0; vi < r; ++vi) {
         const int h = hq * r + vi;
         const long so = (blk * a.h_v + h) * (long)DV * DK;
-        float dS[B::NR][4];
+        f32x4 dS[B::NR];
         if constexpr (CLEAN) {
             b.load_state(dS, a.dh + so);
             b.template run<true>(a.st[0], p0, h, hq, a.seeds + so, a.dh + so, dS, vi > 0);
         } else {
-            float acc[B::NR][4] = {};
+            f32x4 acc[B::NR] = {};
             for (int v = 1; v <= a.n_views; ++v) {
                 b.template run<false>(a.st[v], p0, h, hq, a.seeds + so, a.dh + so, dS, vi > 0);
 #pragma unroll

@@ -20,6 +20,20 @@ def to_dev(inp, device="cuda"):
     return {k: (v.to(device) if isinstance(v, torch.Tensor) else v) for k, v in inp.items()}
 
 
+def draw_gates(rng, g, heads):
+    """Log-gates g [B, T, H] with the decays of ``heads``: None leaves a head's as drawn, a number
+    puts them around it, ("single", x) sets one position in sixteen (the first among them) to x."""
+    g = g.clone()
+    for h, m in enumerate(heads):
+        if isinstance(m, tuple):
+            sel = torch.from_numpy(rng.random(g.shape[:2]) < 1 / 16)
+            sel[:, 0] = True
+            g[..., h] = torch.where(sel, torch.tensor(m[1], dtype=g.dtype), g[..., h])
+        elif m is not None:
+            g[..., h] = torch.from_numpy(m * rng.uniform(0.9, 1.1, g.shape[:2])).to(g.dtype)
+    return g
+
+
 STREAM_KEYS = ("q", "k", "v", "g", "beta")
 
 

@@ -12,7 +12,7 @@ import torch
 import oracle
 import paper_2606_01774_amd as bd
 from paper_2606_01774_amd import workloads as W
-from parity_utils import TOL, rel_err
+from parity_utils import TOL, draw_gates, rel_err, unit_errors
 
 pytestmark = pytest.mark.gpu
 
@@ -75,6 +75,41 @@ def test_both_schedules_match_oracle(B, T, hqk, hv, dk, dv, L, dtype, lengths, w
     for name in NAMES:
         e = rel_err(got[name], ref[name])
         assert e <= TOL["f32"], f"{name}: {e:.2e}"   # everything is fp32 whatever the input type
+
+
+@pytest.mark.parametrize("walk", [False, True])
+@pytest.mark.parametrize("T,dk,dv,L,dtype", [
+    (9, 64, 64, 1, "f32"),
+    (23, 64, 128, 4, "f32"),
+    (82, 64, 64, 16, "f32"),            # a middle state, a short tail block
+    (108, 128, 64, 21, "f32"),          # a middle state off the block's middle
+    (322, 64, 64, 64, "bf16"),          # the longest blocks
+    (190, 128, 128, 37, "bf16"),
+])
+def test_strong_decays(T, dk, dv, L, dtype, walk):
+    """Gates from weak to -20, others in each head and in the two streams: every gradient of every
+    head, dg of order exp(g) among them, is as exact as with weak ones."""
+    clean = [None, -1.0, -3.0, -5.0, -8.0, -20.0, ("single", -12.0), -8.0]
+    noisy = [-5.0, None, -8.0, None, -1.0, ("single", -12.0), -20.0, -8.0]
+    H = len(clean)
+    inp, do, don, h0, dht, _ = _inputs(1, T, H, H, dk, dv, dtype, 90 + T, None)
+    rng = np.random.default_rng(T)
+    inp["g"], inp["gn"] = draw_gates(rng, inp["g"], clean), draw_gates(rng, inp["gn"], noisy)
+    d = {k: v.cuda() for k, v in inp.items()}
+    blocks = -(-T // L)
+    size = _walk_bytes(1, blocks, H, dk, dv)
+    assert size < 2 * blocks * H * dk * dv * 4   # the walk's, and not the parallel schedule's
+    print(f"steps, strong decays: T={T} d={dk}x{dv} L={L} {dtype} walk={walk}", flush=True)
+    got = bd.bdgdn_bwd_train(*[d[k] for k in KEYS], *[d[k + "n"] for k in KEYS], do.cuda(), don.cuda(), block=L,
+                             h0=h0.cuda(), dht=dht.cuda(), want_dh0=True,
+                             workspace=torch.empty(size, dtype=torch.uint8, device="cuda") if walk else None)
+    torch.cuda.synchronize()
+    ref = oracle.bwd_train(*[inp[k] for k in KEYS], *[inp[k + "n"] for k in KEYS], do, don, block=L,
+                           scale=1 / math.sqrt(dk), h0=h0, dht=dht)
+    for name in NAMES:
+        per_token = None if name == "dh0" else got[name].dim() == 3
+        e, unit, n = unit_errors(got[name], ref[name], per_token=per_token)
+        assert n == H and e <= TOL["f32"], f"{name} {unit}: {e:.2e}"
 
 
 def test_views_deterministic_and_match_oracle():
