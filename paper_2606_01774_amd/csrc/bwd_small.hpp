@@ -17,9 +17,14 @@
 // To the clean chunk the rows (q~_t, a_t), (k~_t, b_t) are further readouts of the state before
 // p(t): they add to its gradients
 //     dDelta += XD = Nq^T a + Nk^T b  (Nq = (Q~ K^T) o m),   dK += FA^T Q~ + FB^T K~,
-//     dS0 += Q~^T gp a + K~^T gp b,   and, on the cumulative gate of position p - 1,
-//     v_t = q~_t . (seed a_t) + k~_t . (seed b_t), less sum_t (Nq o FA' + Nk o FB')_tj on that of j
-// (FA', FB' before the mask).  This kernel writes XD for the clean pass, starts the clean dk
+//     dS0 += Q~^T gp a + K~^T gp b,   and, with W = Nq o FA' + Nk o FB' (FA', FB' before the mask),
+//     gp_t (q~_t . S0 a_t + k~_t . S0 b_t) + sum_j W_tj on the cumulative gate of position p(t) - 1,
+//     - W_tj on that of j.
+// dg is the sum of these from the chunk's end back, where every W_tj cancels but for the positions
+// between j and p: both come from one W_tj, since under a strong decay what is left is of the
+// decay's order (a row sum formed as q~ . (FA K), with FA rounded to fp16, left 2^-11 of W whatever
+// the gates: a tenth of dg at g = -5).
+// This kernel writes XD for the clean pass, starts the clean dk
 // and dg with its shares, and runs the clean preparation (the dh-independent part of dS0, U K)
 // with dDelta's share XD included; the clean pass then adds to dk and dg.
 //
@@ -52,8 +57,9 @@ struct SmallSmem {
     float Gp[NP], gp[NP];     // log gamma_(p-1), gamma_(p-1)
     float dB[NP];
     // per-wave partial sums over columns, added in a fixed order at the end: the gate terms of
-    // dA, q~ . seed a, k~ . seed b, dDelta~ . Delta~, and the clean gates' column sums
+    // dA, gp q~ . S0 a, gp k~ . S0 b, dDelta~ . Delta~, and the column sums of W
     float part[kWaves][NP], pA[kWaves][NP], pB[kWaves][NP], pW[kWaves][NP], pC[kWaves][NP];
+    float pR[2][2][NP];   // row sums of W: a's and b's, over 16 columns each
 };
 static_assert(sizeof(SmallSmem) <= 160 * 1024, "one workgroup's LDS");
 static_assert(2 * NP * LDF * 4 <= NP * LDH * 2, "two fp32 matrices in the room of a row block");
@@ -310,7 +316,7 @@ template <typename Od> __global__ void __launch_bounds__(512) bdgdn_bwd_small_ke
         }
         __syncthreads();
         // ---- Gram tiles over the columns: FA and dPh (waves 0 .. 3), FB and dT (waves 4 .. 7), with
-        // the clean gates' column sums; fp32 copies of T~ and M~^T
+        // the row and column sums of W; fp32 copies of T~ and M~^T
         {
             const int m0 = 16 * ((wave >> 1) & 1), n0 = 16 * (wave & 1), i = n0 + rr;
             const bool lo = wave < 4;
@@ -322,7 +328,10 @@ template <typename Od> __global__ void __launch_bounds__(512) bdgdn_bwd_small_ke
             for (int j = 0; j < 4; ++j) {
                 const int t = m0 + 4 * g4 + j;
                 const float m = i < (t & ~(nl - 1)) ? ex(sm.Gp[t] - sm.G[i]) : 0.f, x = lo ? sm.sg[t] * f[j] : f[j];
-                colw = fmaf(x, (float)(lo ? sm.Nq : sm.Nk)[t * LDM + i], colw);
+                const float w = x * (float)(lo ? sm.Nq : sm.Nk)[t * LDM + i];
+                colw += w;
+                const float roww = row_total(w);
+                if (rr == 15) sm.pR[wave >> 2][wave & 1][t] = roww;
                 (lo ? sm.FA : sm.FB)[t * LDM + i] = (_Float16)(x * m);
                 if (lo)
                     dPh[t * LDM + i] = (_Float16)((t ^ i) < nl ? s * e[j] * sm.Dn[i] : 0.f);
@@ -355,16 +364,15 @@ template <typename Od> __global__ void __launch_bounds__(512) bdgdn_bwd_small_ke
             for (int tm = 0; tm < 2; ++tm) {
                 const f32x4 gq = ld4(sm.gp + 16 * tm + 4 * g4);
                 f32x4 ca = tile_mma<_Float16, DD>(z, sm.dOn + 16 * tm * LDH, LDH, sm.S0 + c0 * LDH, LDH, lane);
-                ca = apply(sm.FA, 16 * tm, kq, gq * ld4(sm.sg + 16 * tm + 4 * g4) * ca, lane);
-                f32x4 cb = tile_mma<_Float16, DD>(z, sm.Bn + 16 * tm * LDH, LDH, sm.S0 + c0 * LDH, LDH, lane);
-                cb = apply(sm.FB, 16 * tm, kq, gq * cb, lane);
+                ca = gq * ld4(sm.sg + 16 * tm + 4 * g4) * ca;
+                f32x4 cb = gq * tile_mma<_Float16, DD>(z, sm.Bn + 16 * tm * LDH, LDH, sm.S0 + c0 * LDH, LDH, lane);
 #pragma unroll
                 for (int j = 0; j < 4; ++j) {
                     rowa[tm][j] = ca[j] * (float)qnq[tm][j];
                     rowb[tm][j] = cb[j] * (float)knq[tm][j];
                 }
-                ca = apply(dPh, 16 * tm, knq, ca, lane);
-                dk[tm] = apply_t(dPh, LDM, 16 * tm, qnq, cb, lane);
+                ca = apply(dPh, 16 * tm, knq, apply(sm.FA, 16 * tm, kq, ca, lane), lane);
+                dk[tm] = apply_t(dPh, LDM, 16 * tm, qnq, apply(sm.FB, 16 * tm, kq, cb, lane), lane);
                 const f32x4 xk = apply_t(sm.FB, LDM, 16 * tm, knq, apply_t(sm.FA, LDM, 16 * tm, qnq, z, lane), lane);
 #pragma unroll
                 for (int j = 0; j < 4; ++j) {
@@ -451,6 +459,8 @@ template <typename Od> __global__ void __launch_bounds__(512) bdgdn_bwd_small_ke
                     xp += sm.part[w][lane];
                     xc += sm.pC[w][lane];
                 }
+                xa += sm.pR[0][0][lane] + sm.pR[0][1][lane];
+                xb += sm.pR[1][0][lane] + sm.pR[1][1][lane];
             }
             if (wave == 0) {
                 // noisy: row terms summed from the block's end back, the block-end terms of all its rows

@@ -10,7 +10,7 @@ import torch
 import oracle
 import paper_2606_01774_amd as bd
 from paper_2606_01774_amd import workloads as W
-from parity_utils import TOL, rel_err
+from parity_utils import TOL, draw_gates, rel_err, unit_errors
 
 pytestmark = pytest.mark.gpu
 
@@ -18,9 +18,11 @@ NAMES = ("dq", "dk", "dv", "dg", "dbeta", "dqn", "dkn", "dvn", "dgn", "dbetan", 
 KEYS = ("q", "k", "v", "g", "beta")
 
 
-def _case(B, T, hqk, hv, L, lengths=None, out=torch.float32):
+def _case(B, T, hqk, hv, L, lengths=None, out=torch.float32, gates=None):
     inp = W.make_custom_train(B, T, hqk, hv, 128, 128, "bf16", seed=T + L, lengths=lengths)
     rng = np.random.default_rng(T + L + 1)
+    if gates is not None:
+        inp["g"], inp["gn"] = draw_gates(rng, inp["g"], gates[0]), draw_gates(rng, inp["gn"], gates[1])
     n = B if lengths is None else len(lengths)
     do, don = (torch.from_numpy(rng.standard_normal((B, T, hv, 128)).astype(np.float32)).to(out) for _ in range(2))
     h0 = torch.from_numpy((0.3 * rng.standard_normal((n, hv, 128, 128))).astype(np.float32))
@@ -62,6 +64,21 @@ def test_small_blocks_match_oracle(B, T, hqk, hv, L, lengths, out):
     print(f"small blocks B={B} T={T} h={hqk}/{hv} L={L} {lengths}", flush=True)
     run, _, _, ref = _case(B, T, hqk, hv, L, lengths, out)
     _check(run(), ref)
+
+
+@pytest.mark.parametrize("L", [1, 4, 16])
+def test_strong_decays(L):
+    """Clean gates from weak to -8, others in each head, beside weak and strong noisy ones: every
+    gradient of every head, the clean dg of order exp(g) among them, within the tolerance."""
+    # no head has both streams below -5: its dh0, of order exp(-8) / 128, would be at fp16's spacing
+    clean = [None, -1.0, -2.0, -5.0, -8.0, ("single", -8.0), -5.0, -3.0]
+    noisy = [-5.0, None, None, None, None, None, -5.0, -1.0]
+    print(f"small blocks, strong decays: L={L}", flush=True)
+    run, _, _, ref = _case(1, 200, 8, 8, L, gates=(clean, noisy))
+    got = run()
+    for name in NAMES:
+        e, unit, n = unit_errors(got[name], ref[name], per_token=None if name == "dh0" else got[name].dim() == 3)
+        assert n == 8 and e <= TOL["bf16"], f"{name} {unit}: {e:.2e}"
 
 
 @pytest.mark.parametrize("B,T,hqk,hv,L,lengths", [
