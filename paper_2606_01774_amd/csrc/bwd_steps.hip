@@ -619,12 +619,10 @@ template <typename In, typename Out, int DK, int DV> struct Block {
             }
             flush(dk, qks, i0, cnt, add);
         }
-        // dv = beta w; dbeta and dg from the waves' sums
-        for (int e = tid; e < n * (DV / 4); e += NT) {
-            const int r = e / (DV / 4), c = e % (DV / 4) * 4;
-            const f32x4 x = *reinterpret_cast<const f32x4 *>(s.w + r * DV + c);
-            const float b = s.be[r];
-            st4(st.dv + vo + r * vs + c, b * x[0], b * x[1], b * x[2], b * x[3]);
+        // dv = beta w, by floats (the gradients may lie at any of them); dbeta and dg from the waves' sums
+        for (int e = tid; e < n * DV; e += NT) {
+            const int r = e / DV, c = e % DV;
+            st.dv[vo + r * vs + c] = s.be[r] * s.w[r * DV + c];
         }
         if (tid < n) {
             float b = 0.f, x = 0.f;

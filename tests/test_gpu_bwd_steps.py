@@ -136,3 +136,29 @@ def test_views_deterministic_and_match_oracle():
         for n in ("dq", "dk", "dv", "dg", "dbeta"):
             assert rel_err(runs[0][1][i][n], ref_v[i][n]) <= TOL["f32"], (i, n)
             assert torch.equal(runs[0][1][i][n], runs[1][1][i][n]), (i, n)
+
+
+@pytest.mark.parametrize("T,d,L,dtype", [
+    (70, 64, 16, "f32"),       # per-step
+    (70, 128, 32, "bf16"),     # block form, and on chunks, and in halves
+    (70, 128, 4, "bf16"),
+    (70, 128, 64, "bf16"),
+])
+def test_gradients_at_any_float(T, d, L, dtype):
+    """The gradient buffers need no more alignment than a float: one float past a 16-byte boundary the
+    results are the same bits."""
+    inp, do, don, h0, dht, _ = _inputs(1, T, 1, 2, d, d, dtype, 60 + L, None)
+    dev = {k: v.cuda() for k, v in inp.items()}
+    args = [dev[k] for k in KEYS] + [dev[k + "n"] for k in KEYS] + [do.cuda(), don.cuda()]
+    kw = dict(block=L, h0=h0.cuda(), dht=dht.cuda(), want_dh0=True)
+    print(f"gradients one float off: d={d} L={L} {dtype}", flush=True)
+    want = bd.bdgdn_bwd_train(*args, **kw)
+    grads = {}
+    for name, x in want.items():
+        grads[name] = torch.empty(x.numel() + 4, device="cuda")[1:1 + x.numel()].view(x.shape)
+        assert grads[name].data_ptr() % 16 == 4
+    got = bd.bdgdn_bwd_train(*args, grads=grads, **kw)
+    torch.cuda.synchronize()
+    for name in NAMES:
+        assert got[name].data_ptr() == grads[name].data_ptr()
+        assert torch.equal(got[name], want[name]), name
