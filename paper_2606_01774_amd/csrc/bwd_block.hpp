@@ -321,7 +321,6 @@ template <typename Od, bool PREP> __global__ void __launch_bounds__(512, 4) bdgd
         f16x4 dl[2], dd[2], bq[2];
         {
             const f16x4 dob[2] = {op_tr(sm.dOn, LDH, 0, c0, lane), op_tr(sm.dOn, LDH, 16, c0, lane)};
-            f16x4 aq[2];
 #pragma unroll
             for (int tm = 0; tm < 2; ++tm) {
                 put_tile(sm.Rn, LDH, 16 * tm, col, rn[tm], g4);
@@ -334,7 +333,6 @@ template <typename Od, bool PREP> __global__ void __launch_bounds__(512, 4) bdgd
                     roww[tm][j] = d[j] * dn[j];
                     settle(roww[tm][j]);
                 }
-                aq[tm] = scale4(dob[tm], f32x4{sgn, sgn, sgn, sgn});
             }
 #pragma unroll
             for (int tm = 0; tm < 2; ++tm) {
@@ -374,19 +372,19 @@ template <typename Od, bool PREP> __global__ void __launch_bounds__(512, 4) bdgd
                                           op_tr(sm.Mc, LDM, 16, 16 * tm, lane), z);
                     put_uk(uk, tm, wave, lane, h4(f * u));
                 }
-                // the c term
+                // the c term; s gamma~_n on the fp32 product, not on the fp16 rows
 #pragma unroll
                 for (int tm = 0; tm < 8; ++tm) {
-                    f32x4 c = apply_t(sm.K, LDH, 16 * tm, drq, z, lane);
+                    f32x4 c = sgn * apply_t(sm.Qn, LDH, 16 * tm, dob, z, lane);
+                    c = apply_t(sm.K, LDH, 16 * tm, drq, c, lane);
                     c = apply_t(sm.Q, LDH, 16 * tm, sd, c, lane);
-                    c = apply_t(sm.Qn, LDH, 16 * tm, aq, c, lane);
                     ct[tm * 8 * 64] = h4(apply_t(sm.Kn, LDH, 16 * tm, bq, c, lane));
                 }
                 if (tid == 0) a.gnb[uw] = ex(Ge);
             } else {
 #pragma unroll
                 for (int tm = 0; tm < 8; ++tm) {
-                    const f32x4 c = apply_t(sm.Qn, LDH, 16 * tm, aq, z, lane);
+                    const f32x4 c = sgn * apply_t(sm.Qn, LDH, 16 * tm, dob, z, lane);
                     ct[tm * 8 * 64] = h4(f4(ct[tm * 8 * 64]) + apply_t(sm.Kn, LDH, 16 * tm, bq, c, lane));
                 }
             }

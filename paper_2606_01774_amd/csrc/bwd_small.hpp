@@ -221,7 +221,7 @@ template <typename Od> __global__ void __launch_bounds__(512) bdgdn_bwd_small_ke
         {
             const f32x4 b0 = ld4(sm.bet + 4 * g4), b1 = ld4(sm.bet + 16 + 4 * g4);
             const f32x4 bn0 = ld4(sm.betn + 4 * g4), bn1 = ld4(sm.betn + 16 + 4 * g4);
-            f16x4 dl[2], rn[2], dd[2], aq[2], bq[2];
+            f16x4 dl[2], rn[2], dd[2], aq[2], bq[2], ag[2], al[2], bg[2];   // ag + al, bg: gp a, gp b
             f32x4 dn[2];
 #pragma unroll
             for (int tm = 0; tm < 2; ++tm) {
@@ -246,7 +246,13 @@ template <typename Od> __global__ void __launch_bounds__(512) bdgdn_bwd_small_ke
                 put_tile(sm.dDn, LDH, 16 * tm, col, dd[tm], g4);
 #pragma unroll
                 for (int j = 0; j < 4; ++j) roww[tm][j] = d[j] * dn[tm][j];
-                aq[tm] = scale4(dob[tm], ld4(sm.sg + 16 * tm + 4 * g4));
+                const f32x4 sg = ld4(sm.sg + 16 * tm + 4 * g4);
+                aq[tm] = scale4(dob[tm], sg);
+                // gp a goes into the state gradient in two fp16 parts: the block by block backward
+                // scales the product instead, which has one factor per block
+                const f32x4 x = ld4(sm.gp + 16 * tm + 4 * g4) * sg * f4(dob[tm]);
+                ag[tm] = h4(x);
+                al[tm] = h4(x - f4(ag[tm]));
             }
 #pragma unroll
             for (int tm = 0; tm < 2; ++tm) {   // dR~ = T~^T dDelta~ (T~^T_ri = beta~_r M~_ir)
@@ -259,7 +265,9 @@ template <typename Od> __global__ void __launch_bounds__(512) bdgdn_bwd_small_ke
                     const int t = 16 * tm + 4 * g4 + j;
                     if (t < nvalid) pn.dv[(long)t * vs + col] = c[j] * inv;
                 }
-                bq[tm] = h4(-ld4(sm.gamn + 16 * tm + 4 * g4) * c);
+                const f32x4 x = -ld4(sm.gamn + 16 * tm + 4 * g4) * c;
+                bq[tm] = h4(x);
+                bg[tm] = h4(ld4(sm.gp + 16 * tm + 4 * g4) * x);
                 put_tile(sm.Bn, LDH, 16 * tm, col, bq[tm], g4);
             }
             // XD (for the clean pass), Y = s P^T dO + XD, -Gamma T^T Y
@@ -280,9 +288,6 @@ template <typename Od> __global__ void __launch_bounds__(512) bdgdn_bwd_small_ke
                                       scale4(op_tr(sm.Mc, LDM, 16, 16 * tm, lane), bb), yq[0], yq[1], z);
                 drq[tm] = h4(-gm * c);
                 sd[tm] = scale4(doc[tm], s * gm);
-                const f32x4 gq = ld4(sm.gp + 16 * tm + 4 * g4);
-                aq[tm] = scale4(aq[tm], gq);
-                bq[tm] = scale4(bq[tm], gq);
             }
             // c term: K^T (-Gamma dR0) + Q^T (s Gamma dO) + Q~^T (gp a) + K~^T (gp b)
             f16x4 *ct = reinterpret_cast<f16x4 *>(a.cterm + (size_t)uw * DD * DD) + wave * 64 + lane;
@@ -290,8 +295,9 @@ template <typename Od> __global__ void __launch_bounds__(512) bdgdn_bwd_small_ke
             for (int tm = 0; tm < 8; ++tm) {
                 f32x4 c = apply_t(sm.K, LDH, 16 * tm, drq, z, lane);
                 c = apply_t(sm.Q, LDH, 16 * tm, sd, c, lane);
-                c = apply_t(sm.Qn, LDH, 16 * tm, aq, c, lane);
-                ct[tm * 8 * 64] = h4(apply_t(sm.Kn, LDH, 16 * tm, bq, c, lane));
+                c = apply_t(sm.Qn, LDH, 16 * tm, ag, c, lane);
+                c = apply_t(sm.Qn, LDH, 16 * tm, al, c, lane);
+                ct[tm * 8 * 64] = h4(apply_t(sm.Kn, LDH, 16 * tm, bg, c, lane));
             }
             // U K = Gamma diag(beta) M^T (D K)
             const float Ge = sm.G[NP - 1];

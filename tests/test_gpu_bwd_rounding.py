@@ -1,0 +1,56 @@
+"""Roundings on the way to a gradient of the block-form backward, by the 2-norm of its error
+against the fp64 oracle: with bf16 upstream gradients (exact in fp16) the error is that of the
+fp16 roundings in between, each of relative RMS 2^-11 / sqrt(3) times the RMS of 1 / x over a
+binade of log-uniform x, 2.1e-4, and independent ones add in squares."""
+import math
+
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_2606_01774_amd as bd
+from paper_2606_01774_amd import workloads as W
+from parity_utils import draw_gates
+
+pytestmark = pytest.mark.gpu
+
+KEYS = ("q", "k", "v", "g", "beta")
+ONE = 2.0 ** -11 / math.sqrt(3) * math.sqrt(0.375 / math.log(2))
+
+
+def _errors(L, clean, noisy, with_clean, T=96, seeds=4):
+    """Relative 2-norm error of every gradient over all heads and seeds; the clean readout's
+    upstream gradient zero unless with_clean."""
+    H, num, den = len(clean), {}, {}
+    for seed in range(seeds):
+        inp = W.make_custom_train(1, T, H, H, 128, 128, "bf16", seed=300 + seed)
+        rng = np.random.default_rng(400 + seed)
+        inp["g"], inp["gn"] = draw_gates(rng, inp["g"], clean), draw_gates(rng, inp["gn"], noisy)
+        do, don = (torch.from_numpy(rng.standard_normal((1, T, H, 128)).astype(np.float32)).bfloat16()
+                   for _ in range(2))
+        if not with_clean:
+            do = torch.zeros_like(do)
+        got = bd.bdgdn_bwd_train(*[inp[k].cuda() for k in KEYS], *[inp[k + "n"].cuda() for k in KEYS], do.cuda(),
+                                 don.cuda(), block=L, want_dh0=True)
+        torch.cuda.synchronize()
+        ref = oracle.bwd_train(*[inp[k] for k in KEYS], *[inp[k + "n"] for k in KEYS], do, don, block=L,
+                               scale=1 / math.sqrt(128))
+        for name, x in ref.items():
+            if not x.any():
+                continue   # dq without a clean readout
+            axes = tuple(i for i in range(x.ndim) if i != (1 if name == "dh0" else 2))
+            d = got[name].double().cpu().numpy() - x
+            scale = (x * x).mean(axis=axes)   # each head by its own size
+            num[name] = num.get(name, 0) + ((d * d).mean(axis=axes) / scale).mean() / seeds
+    err = {name: math.sqrt(x) for name, x in num.items()}
+    print(f"L={L}", {name: f"{x:.2e}" for name, x in err.items()}, flush=True)
+    return err
+
+
+@pytest.mark.parametrize("L", [2, 16, 32])
+def test_seed_gradient_rounds_the_upstream_rows_once(L):
+    """dh0 from the noisy readout under strong clean decays, s gamma~_n Q~^T dO~ and a part through the
+    keys a few times smaller: one rounding, of the sum.  Scaling the rows in fp16 was a second one."""
+    err = _errors(L, [-4.0] * 4, [None] * 4, False)
+    assert err["dh0"] <= 1.2 * ONE
