@@ -652,7 +652,7 @@ static bdgdn_fwd_desc_t bwd_sub(const bdgdn_fwd_desc_t *d)
 // uses as fp16 operands only), U K (32 x d_k, fp16), gamma_n (fp32); then the range pass's
 // per-block maxima and {sigma, 1 / sigma}.  Byte offsets, each aligned to 256.
 // Small blocks in chunks: also the clean dDelta's share of each chunk's noisy blocks (xd, 32 x
-// d_v, fp16).
+// d_v, fp32: a part of a sum).
 struct BwdLayout {
     size_t seeds, cterm, uk, gnb, part, range, xd, total;
 };
@@ -668,7 +668,7 @@ static BwdLayout bwd_layout_units(size_t units, const bdgdn_fwd_desc_t *d, size_
     l.part = l.gnb + up256(units * 4);
     l.range = l.part + up256(kRangeBlocks * 4);
     l.xd = l.range + 256;
-    l.total = l.xd + (small ? up256(units * 32 * d->d_v * 2) : 0);
+    l.total = l.xd + (small ? up256(units * 32 * d->d_v * 4) : 0);
     return l;
 }
 static BwdLayout bwd_layout(const bdgdn_fwd_desc_t *d)
@@ -928,7 +928,7 @@ static int bwd_impl(const bdgdn_fwd_desc_t *desc, const void *q, const void *k, 
     a.h_qk = desc->h_qk; a.h_v = desc->h_v;
     a.scale = desc->scale;
     a.nl = small ? desc->block : 0;
-    a.xd = reinterpret_cast<_Float16 *>(ws + lay.xd);
+    a.xd = reinterpret_cast<float *>(ws + lay.xd);
     const long rows = (long)desc->batch * desc->seqlen;
     // the range of the upstream gradients: the power-of-two scale they enter the kernels with
     RangeArgs ra = {};

@@ -48,9 +48,9 @@ struct BwdArgs {
     int T, nblk, L, h_qk, h_v;
     float scale;
     // noisy blocks of nl positions (a power of two <= 16) in clean chunks of L = 32, or 0; xd
-    // [unit][2 tiles][8 waves][64 lanes][4] fp16: their share of the chunk's dDelta
+    // [unit][2 tiles][8 waves][64 lanes][4] fp32: their share of the chunk's dDelta
     int nl;
-    _Float16 *xd;
+    float *xd;
 };
 // A further noisy view (the complementary-view backward): its inputs, the upstream gradient
 // of its readout and its gradients, laid out as the noisy stream of BwdArgs.

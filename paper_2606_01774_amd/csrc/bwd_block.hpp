@@ -620,7 +620,7 @@ template <typename Od, bool SMALL> __global__ void __launch_bounds__(512, 4) bdg
                     dlast -= rowg[tm][j];
                 }
                 if constexpr (SMALL)
-                    d += f4((reinterpret_cast<const f16x4 *>(a.xd + (size_t)uw * NP * DD) + tid)[tm * 8 * 64]);
+                    d += (reinterpret_cast<const f32x4 *>(a.xd + (size_t)uw * NP * DD) + tid)[tm * 8 * 64];
                 dd[tm] = h4(d);
                 put_tile(sm.dDl, LDH, 16 * tm, col, dd[tm], g4);
             }

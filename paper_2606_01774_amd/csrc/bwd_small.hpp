@@ -221,7 +221,8 @@ template <typename Od> __global__ void __launch_bounds__(512) bdgdn_bwd_small_ke
         {
             const f32x4 b0 = ld4(sm.bet + 4 * g4), b1 = ld4(sm.bet + 16 + 4 * g4);
             const f32x4 bn0 = ld4(sm.betn + 4 * g4), bn1 = ld4(sm.betn + 16 + 4 * g4);
-            f16x4 dl[2], rn[2], dd[2], aq[2], bq[2], ag[2], al[2], bg[2];   // ag + al, bg: gp a, gp b
+            // a (not b, a result of other fp16 products) in two fp16 parts; ga, gb: gp a, gp b
+            f16x4 dl[2], rn[2], dd[2], aq[2], al[2], bq[2], ga[2], gal[2], gb[2];
             f32x4 dn[2];
 #pragma unroll
             for (int tm = 0; tm < 2; ++tm) {
@@ -246,13 +247,14 @@ template <typename Od> __global__ void __launch_bounds__(512) bdgdn_bwd_small_ke
                 put_tile(sm.dDn, LDH, 16 * tm, col, dd[tm], g4);
 #pragma unroll
                 for (int j = 0; j < 4; ++j) roww[tm][j] = d[j] * dn[tm][j];
-                const f32x4 sg = ld4(sm.sg + 16 * tm + 4 * g4);
-                aq[tm] = scale4(dob[tm], sg);
-                // gp a goes into the state gradient in two fp16 parts: the block by block backward
-                // scales the product instead, which has one factor per block
-                const f32x4 x = ld4(sm.gp + 16 * tm + 4 * g4) * sg * f4(dob[tm]);
-                ag[tm] = h4(x);
-                al[tm] = h4(x - f4(ag[tm]));
+                // a = s gamma~_n dO~ differs by block, so that it can't be put on a product of dO~ as the
+                // block by block backward does
+                const f32x4 x = ld4(sm.sg + 16 * tm + 4 * g4) * f4(dob[tm]);
+                aq[tm] = h4(x);
+                al[tm] = h4(x - f4(aq[tm]));
+                const f32x4 y = ld4(sm.gp + 16 * tm + 4 * g4) * x;
+                ga[tm] = h4(y);
+                gal[tm] = h4(y - f4(ga[tm]));
             }
 #pragma unroll
             for (int tm = 0; tm < 2; ++tm) {   // dR~ = T~^T dDelta~ (T~^T_ri = beta~_r M~_ir)
@@ -267,17 +269,19 @@ template <typename Od> __global__ void __launch_bounds__(512) bdgdn_bwd_small_ke
                 }
                 const f32x4 x = -ld4(sm.gamn + 16 * tm + 4 * g4) * c;
                 bq[tm] = h4(x);
-                bg[tm] = h4(ld4(sm.gp + 16 * tm + 4 * g4) * x);
+                gb[tm] = h4(ld4(sm.gp + 16 * tm + 4 * g4) * x);
                 put_tile(sm.Bn, LDH, 16 * tm, col, bq[tm], g4);
             }
             // XD (for the clean pass), Y = s P^T dO + XD, -Gamma T^T Y
             const f16x4 doc[2] = {op_tr(sm.dO, LDH, 0, c0, lane), op_tr(sm.dO, LDH, 16, c0, lane)};
             f16x4 yq[2], drq[2], sd[2];
-            f16x4 *xd = reinterpret_cast<f16x4 *>(a.xd + (size_t)uw * NP * DD) + wave * 64 + lane;
+            f32x4 *xd = reinterpret_cast<f32x4 *>(a.xd + (size_t)uw * NP * DD) + wave * 64 + lane;
 #pragma unroll
             for (int tm = 0; tm < 2; ++tm) {
-                const f32x4 x = apply_t(sm.Nk, LDM, 16 * tm, bq, apply_t(sm.Nq, LDM, 16 * tm, aq, z, lane), lane);
-                xd[tm * 8 * 64] = h4(x);
+                f32x4 x = apply_t(sm.Nq, LDM, 16 * tm, aq, z, lane);
+                x = apply_t(sm.Nq, LDM, 16 * tm, al, x, lane);
+                x = apply_t(sm.Nk, LDM, 16 * tm, bq, x, lane);
+                xd[tm * 8 * 64] = x;
                 yq[tm] = h4(s * apply_t(sm.Ph, LDM, 16 * tm, doc, z, lane) + x);
             }
 #pragma unroll
@@ -295,9 +299,9 @@ template <typename Od> __global__ void __launch_bounds__(512) bdgdn_bwd_small_ke
             for (int tm = 0; tm < 8; ++tm) {
                 f32x4 c = apply_t(sm.K, LDH, 16 * tm, drq, z, lane);
                 c = apply_t(sm.Q, LDH, 16 * tm, sd, c, lane);
-                c = apply_t(sm.Qn, LDH, 16 * tm, ag, c, lane);
-                c = apply_t(sm.Qn, LDH, 16 * tm, al, c, lane);
-                ct[tm * 8 * 64] = h4(apply_t(sm.Kn, LDH, 16 * tm, bg, c, lane));
+                c = apply_t(sm.Qn, LDH, 16 * tm, ga, c, lane);
+                c = apply_t(sm.Qn, LDH, 16 * tm, gal, c, lane);
+                ct[tm * 8 * 64] = h4(apply_t(sm.Kn, LDH, 16 * tm, gb, c, lane));
             }
             // U K = Gamma diag(beta) M^T (D K)
             const float Ge = sm.G[NP - 1];

@@ -54,3 +54,12 @@ def test_seed_gradient_rounds_the_upstream_rows_once(L):
     keys a few times smaller: one rounding, of the sum.  Scaling the rows in fp16 was a second one."""
     err = _errors(L, [-4.0] * 4, [None] * 4, False)
     assert err["dh0"] <= 1.2 * ONE
+
+
+@pytest.mark.parametrize("L", [2, 16])
+def test_noisy_blocks_in_a_chunk_round_once_per_factor(L):
+    """dv from the noisy readout under strong clean decays, mostly the share of the noisy blocks of
+    the same chunk (Q~ K^T)^T a: three roundings (the Gram entries, the sum, its part through the
+    noisy keys' own) and smaller ones.  Rounding a = s gamma~_n dO~ to fp16 was a fourth."""
+    err = _errors(L, [-4.0] * 4, [None] * 4, False)
+    assert err["dv"] <= 1.9 * ONE
