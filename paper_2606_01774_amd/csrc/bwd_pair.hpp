@@ -20,7 +20,10 @@
 //
 // The gate gradients of a half: its rows' terms as in a block of its own, and on its last
 // position <gamma~_n dS~, seed>, which is sum over the rows of q~ . (dQ~'s terms with the half's
-// seed), for half a also that of k~b . (ea Bb S0^T).
+// seed), for half a also that of k~b . (ea Bb S0^T).  The terms dDelta~ . Delta~ of the rows, added on
+// the last position and taken off at their own, are summed over the rows before each position, in
+// fp32: a difference would leave their rounding under strong decays, and factors rounded to fp16
+// more of it (dg~ 15 % further from 64 bits at gates of -1 to -5).
 //
 // One workgroup per CU (157 KB of LDS), bound by what it waits for: 30 us a unit, of which
 // its 430 KB of HBM traffic are 22 at a large copy's rate, which do not overlap the barriers
@@ -47,11 +50,11 @@ struct PairSmem {
     float G[2][NP], G2[2][NP], gam[2][NP], bet[2][NP];
     float dB[2][NP];
 };
-// per-wave partial sums over columns (in Rn): by row the gate terms of dA and k~ . (dK~'s seed
-// terms) - dDelta~ . Delta~; over all rows a wave's share of the terms of a's and b's last
+// per-wave partial sums over columns (in Rn): by row the gate terms of dA, k~ . (dK~'s seed
+// terms) and dDelta~ . Delta~; over all rows a wave's share of the seed terms of a's and b's last
 // position; by eight rows dbeta from dT
 struct PairSums {
-    float part[16][NP], b[16][NP], end[2][16], db[2][4][NP];
+    float part[16][NP], b[16][NP], w[16][NP], end[2][16], db[2][4][NP];
 };
 static_assert(sizeof(PairSmem) <= 160 * 1024, "one workgroup's LDS");
 static_assert(sizeof(PairSums) <= 2 * NP * LDH * 2 && 2 * NP * LDF * 4 <= 4 * NP * LDM * 2 &&
@@ -252,7 +255,8 @@ template <typename Od, bool PREP> __global__ void __launch_bounds__(1024) bdgdn_
         // ---- this wave's columns: the clean preparation of its half; half a: R~a, Delta~a, half b:
         // dDelta~b, dV~b, Bb
         f32x4 acc[8];   // half a: its clean c term, completed below
-        f16x4 dl[2], dd[2], bq[2];
+        f32x4 first[2];   // Delta~a (half a), dDelta~b (half b): fp32 for the row sums with the other
+        f16x4 dd[2], bq[2];
 #pragma unroll
         for (int tm = 0; tm < 8; ++tm) acc[tm] = z;
         if constexpr (PREP) {
@@ -293,7 +297,6 @@ template <typename Od, bool PREP> __global__ void __launch_bounds__(1024) bdgdn_
                     ct[tm * 8 * 64] = h4(c);
             }
         }
-        float roww[2][4];
         if (x == 0) {
 #pragma unroll
             for (int tm = 0; tm < 2; ++tm)
@@ -301,15 +304,17 @@ template <typename Od, bool PREP> __global__ void __launch_bounds__(1024) bdgdn_
 #pragma unroll
             for (int tm = 0; tm < 2; ++tm) {
                 put_tile(Rx, LDH, 16 * tm, col, bq[tm], g4);
-                dl[tm] = h4(apply_T(sm.Mn[0], sm.betn[0], 16 * tm, bq, lane));
+                first[tm] = apply_T(sm.Mn[0], sm.betn[0], 16 * tm, bq, lane);
             }
         } else {
             const f16x4 da[2] = {op_tr(sm.dOn, LDH, 0, c0, lane), op_tr(sm.dOn, LDH, 16, c0, lane)};
             const f16x4 db[2] = {op_tr(sm.dOn, LDH, 32, c0, lane), op_tr(sm.dOn, LDH, 48, c0, lane)};
 #pragma unroll
-            for (int tm = 0; tm < 2; ++tm)
-                dd[tm] = h4(s * ld4(sm.Dn[1] + 16 * tm + 4 * g4) *
-                            apply(sm.Pn[3], 16 * tm, db, apply(sm.Pn[2], 16 * tm, da, z, lane), lane));
+            for (int tm = 0; tm < 2; ++tm) {
+                first[tm] = s * ld4(sm.Dn[1] + 16 * tm + 4 * g4) *
+                            apply(sm.Pn[3], 16 * tm, db, apply(sm.Pn[2], 16 * tm, da, z, lane), lane);
+                dd[tm] = h4(first[tm]);
+            }
         }
         // dR~ = T~^T dDelta~ (= dV~) and B = -Gamma~ dR~ of this wave's half
         auto half_back = [&]() {
@@ -329,7 +334,7 @@ template <typename Od, bool PREP> __global__ void __launch_bounds__(1024) bdgdn_
 #pragma unroll
         for (int tm = 0; tm < 2; ++tm) {
             if (x == 0) {
-                put_tile(sm.X1, LDH, 16 * tm, col, dl[tm], g4);
+                put_tile(sm.X1, LDH, 16 * tm, col, h4(first[tm]), g4);
             } else {
                 put_tile(sm.X2, LDH, NP + 16 * tm, col, dd[tm], g4);
                 put_tile(sm.X3, LDH, NP + 16 * tm, col, bq[tm], g4);
@@ -350,8 +355,9 @@ template <typename Od, bool PREP> __global__ void __launch_bounds__(1024) bdgdn_
 #pragma unroll
             for (int tm = 0; tm < 2; ++tm) {
                 put_tile(Rx, LDH, 16 * tm, col, rn[tm], g4);
-                dl[tm] = h4(apply_T(sm.Mn[1], sm.betn[1], 16 * tm, rn, lane));
-                put_tile(sm.X1, LDH, NP + 16 * tm, col, dl[tm], g4);
+                const f32x4 d = apply_T(sm.Mn[1], sm.betn[1], 16 * tm, rn, lane);
+                put_tile(sm.X1, LDH, NP + 16 * tm, col, h4(d), g4);
+                first[tm] *= d;
             }
         } else {
             const f16x4 da[2] = {op_tr(sm.dOn, LDH, 0, c0, lane), op_tr(sm.dOn, LDH, 16, c0, lane)};
@@ -360,7 +366,9 @@ template <typename Od, bool PREP> __global__ void __launch_bounds__(1024) bdgdn_
 #pragma unroll
             for (int tm = 0; tm < 2; ++tm) {
                 const f32x4 c = apply(sm.Pn[1], 16 * tm, db, apply(sm.Pn[0], 16 * tm, da, z, lane), lane);
-                dd[tm] = h4(ld4(sm.Dn[0] + 16 * tm + 4 * g4) * apply_t(sm.N, LDM, 16 * tm, bb, s * eb * c, lane));
+                const f32x4 d = ld4(sm.Dn[0] + 16 * tm + 4 * g4) * apply_t(sm.N, LDM, 16 * tm, bb, s * eb * c, lane);
+                dd[tm] = h4(d);
+                first[tm] *= d;
                 put_tile(sm.X2, LDH, 16 * tm, col, dd[tm], g4);
             }
             half_back();
@@ -368,12 +376,7 @@ template <typename Od, bool PREP> __global__ void __launch_bounds__(1024) bdgdn_
             for (int tm = 0; tm < 2; ++tm) put_tile(sm.X3, LDH, 16 * tm, col, bq[tm], g4);
         }
 #pragma unroll
-        for (int tm = 0; tm < 2; ++tm)
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                roww[tm][j] = (float)dd[tm][j] * (float)dl[tm][j];
-                settle(roww[tm][j]);
-            }
+        for (int tm = 0; tm < 2; ++tm) settle(first[tm]);   // now dDelta~ . Delta~, this column's terms
         __syncthreads();
         // ---- half a's waves: the c term of sub-block a; half b's: the Gram tiles over the columns
         float *const dT = reinterpret_cast<float *>(sm.Mc);
@@ -482,8 +485,7 @@ template <typename Od, bool PREP> __global__ void __launch_bounds__(1024) bdgdn_
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
                 e2 = fmaf(ca[tm][j], (float)qx[j], e2);
-                s4[j] = fmaf(cb[tm][j], (float)kx[j], -roww[tm][j]);
-                (x ? e2 : e1) += roww[tm][j];
+                s4[j] = cb[tm][j] * (float)kx[j];
             }
             rows(o, sm.Kn, NP);
             ca[tm] = apply(sm.Pn[2 * x + 1], 16 * tm, o, ca[tm], lane);
@@ -497,8 +499,11 @@ template <typename Od, bool PREP> __global__ void __launch_bounds__(1024) bdgdn_
             for (int j = 0; j < 4; ++j) {
                 const int t = 16 * tm + 4 * g4 + j;
                 if (t < nvx) dqx[(long)t * qks] = fmaf(ca[tm][j], inv, old[tm][j]);
-                const float t4 = row_total(s4[j]);
-                if (rr == 15) ps.b[wave][t] = t4;
+                const float t4 = row_total(s4[j]), w4 = row_total(first[tm][j]);
+                if (rr == 15) {
+                    ps.b[wave][t] = t4;
+                    ps.w[wave][t] = w4;
+                }
             }
         }
         e1 = wave_total(e1);
@@ -524,15 +529,19 @@ template <typename Od, bool PREP> __global__ void __launch_bounds__(1024) bdgdn_
             }
         }
         if (w == 0) {
-            // dg of a half: row terms summed from its end back, the block-end terms of all rows
-            float g = 0.f, db = 0.f;
+            // dg of a half: row terms summed from its end back, the block-end terms of all rows, and of
+            // dDelta~ . Delta~, a block-end term less a row term, what is left: the rows before
+            float g = 0.f, db = 0.f, before = 0.f;
             if (lane < NP) {
                 db = ((ps.db[x][0][lane] + ps.db[x][1][lane]) + (ps.db[x][2][lane] + ps.db[x][3][lane])) + sm.dB[x][lane];
 #pragma unroll
-                for (int v = 0; v < 8; ++v) g += ps.part[8 * x + v][lane] + ps.b[8 * x + v][lane];
+                for (int v = 0; v < 8; ++v) {
+                    g += ps.part[8 * x + v][lane] + ps.b[8 * x + v][lane];
+                    if (lane > 0) before += ps.w[8 * x + v][lane - 1];
+                }
             }
             const float e = lane < 16 ? ps.end[x][lane] : 0.f;
-            g = back_sum32(g, lane) + wave_total(e);
+            g = back_sum32(g, lane) + wave_total(e) + ut::scan32(before, lane);
             if (lane < nvx) {
                 const long o = (long)(x * a.L + lane) * a.h_v;
                 pn.dg[o] = g * inv;
