@@ -465,16 +465,18 @@ template <typename Od, bool PREP> __global__ void __launch_bounds__(512, 4) bdgd
             }
         }
         if (wave == 0) {
-            // dg: row terms summed from the block's end back, the block-end terms of all rows
-            float x = 0.f, e = 0.f;
+            // dg: row terms summed from the block's end back, the block-end terms of all rows, and of
+            // dDelta~ . Delta~, a block-end term less a row term, what is left: the rows before
+            float x = 0.f, e = 0.f, before = 0.f;
             if (lane < NP) {
 #pragma unroll
                 for (int w = 0; w < kWaves; ++w) {
-                    x += sm.part[w][lane] + sm.pB[w][lane] - sm.pW[w][lane];
-                    e += sm.pA[w][lane] + sm.pW[w][lane];
+                    x += sm.part[w][lane] + sm.pB[w][lane];
+                    e += sm.pA[w][lane];
+                    if (lane > 0) before += sm.pW[w][lane - 1];
                 }
             }
-            x = back_sum32(x, lane) + wave_total(e);
+            x = back_sum32(x, lane) + wave_total(e) + ut::scan32(before, lane);
             if (lane < nvalid) {
                 pn.dg[(long)lane * a.h_v] = x * inv;
                 pn.db[(long)lane * a.h_v] = sm.dB[lane] * inv;
@@ -494,7 +496,10 @@ struct CleanSmem {
     _Float16 Mh[NP * LDM], Ph[NP * LDM], dPh[NP * LDM], Wh[NP * LDM];
     float KK[NP * LDF], dT[NP * LDF];
     float G[NP], G2[NP], gam[NP], bet[NP], dB[NP];
-    float part[kWaves][NP];   // per-wave partial sums of the gate gradient
+    // per-wave partial sums of the gate gradient, which is summed from the block's end back: what a
+    // position would add and take off again is left out, since under strong decays the rest is of the
+    // decay's order and its rounding is not
+    float part[kWaves][NP];
 };
 static_assert(sizeof(CleanSmem) <= 80 * 1024, "two workgroups per CU");
 
@@ -614,9 +619,11 @@ template <typename Od, bool SMALL> __global__ void __launch_bounds__(512, 4) bdg
                 f32x4 d = s * apply_t(sm.Ph, LDM, 16 * tm, doc, z, lane);
 #pragma unroll
                 for (int j = 0; j < 4; ++j) {
-                    const float w = ex(Ge - sm.G[16 * tm + 4 * g4 + j]) * kds[tm][j];
+                    const int t = 16 * tm + 4 * g4 + j;
+                    const float w = ex(Ge - sm.G[t]) * kds[tm][j];
                     d[j] += w;
-                    rowg[tm][j] = -w * (float)dl[j];
+                    // the last position's own term would be taken off itself
+                    rowg[tm][j] = t < NP - 1 ? -w * (float)dl[j] : 0.f;
                     dlast -= rowg[tm][j];
                 }
                 if constexpr (SMALL)
@@ -648,7 +655,8 @@ template <typename Od, bool SMALL> __global__ void __launch_bounds__(512, 4) bdg
             for (int j = 0; j < 4; ++j) {
                 const int t = m0 + 4 * g4 + j;
                 if (lo) {
-                    const float w = s * e[j] * (float)sm.Ph[t * LDM + i];
+                    // the diagonal, in the row and the column sum of one position, is in neither
+                    const float w = i < t ? s * e[j] * (float)sm.Ph[t * LDM + i] : 0.f;
                     sm.dPh[t * LDM + i] = (_Float16)(i <= t ? s * e[j] * ex(sm.G[t] - sm.G[i]) : 0.f);
                     if (wave >> 1)
                         rowg[1][j] += w;

@@ -21,9 +21,9 @@
 //     gp_t (q~_t . S0 a_t + k~_t . S0 b_t) + sum_j W_tj on the cumulative gate of position p(t) - 1,
 //     - W_tj on that of j.
 // dg is the sum of these from the chunk's end back, where every W_tj cancels but for the positions
-// between j and p: both come from one W_tj, since under a strong decay what is left is of the
-// decay's order (a row sum formed as q~ . (FA K), with FA rounded to fp16, left 2^-11 of W whatever
-// the gates: a tenth of dg at g = -5).
+// between j and p: both come from one W_tj, and j = p - 1 is in neither, since under a strong decay
+// what is left is of the decay's order (a row sum formed as q~ . (FA K), with FA rounded to fp16,
+// left 2^-11 of W whatever the gates: a tenth of dg at g = -5).
 // This kernel writes XD for the clean pass, starts the clean dk
 // and dg with its shares, and runs the clean preparation (the dh-independent part of dS0, U K)
 // with dDelta's share XD included; the clean pass then adds to dk and dg.
@@ -59,7 +59,8 @@ struct SmallSmem {
     // per-wave partial sums over columns, added in a fixed order at the end: the gate terms of
     // dA, gp q~ . S0 a, gp k~ . S0 b, dDelta~ . Delta~, and the column sums of W
     float part[kWaves][NP], pA[kWaves][NP], pB[kWaves][NP], pW[kWaves][NP], pC[kWaves][NP];
-    float pR[2][2][NP];   // row sums of W: a's and b's, over 16 columns each
+    // row sums of W, a's and b's, over 16 columns each, but for column p - 1, which is in pD
+    float pR[2][2][NP], pD[2][NP];
 };
 static_assert(sizeof(SmallSmem) <= 160 * 1024, "one workgroup's LDS");
 static_assert(2 * NP * LDF * 4 <= NP * LDH * 2, "two fp32 matrices in the room of a row block");
@@ -338,7 +339,11 @@ template <typename Od> __global__ void __launch_bounds__(512) bdgdn_bwd_small_ke
             for (int j = 0; j < 4; ++j) {
                 const int t = m0 + 4 * g4 + j;
                 const float m = i < (t & ~(nl - 1)) ? ex(sm.Gp[t] - sm.G[i]) : 0.f, x = lo ? sm.sg[t] * f[j] : f[j];
-                const float w = x * (float)(lo ? sm.Nq : sm.Nk)[t * LDM + i];
+                float w = x * (float)(lo ? sm.Nq : sm.Nk)[t * LDM + i];
+                if (i + 1 == (t & ~(nl - 1))) {
+                    sm.pD[wave >> 2][t] = w;
+                    w = 0.f;
+                }
                 colw += w;
                 const float roww = row_total(w);
                 if (rr == 15) sm.pR[wave >> 2][wave & 1][t] = roww;
@@ -471,17 +476,24 @@ template <typename Od> __global__ void __launch_bounds__(512) bdgdn_bwd_small_ke
                 }
                 xa += sm.pR[0][0][lane] + sm.pR[0][1][lane];
                 xb += sm.pR[1][0][lane] + sm.pR[1][1][lane];
+                if (wave == 0 && lane >= nl) {   // the noisy gates' terms hold all of the seed
+                    xa += sm.pD[0][lane];
+                    xb += sm.pD[1][lane];
+                }
             }
             if (wave == 0) {
-                // noisy: row terms summed from the block's end back, the block-end terms of all its rows
-                float x = xp + xb - xw, e = xa + xw;
+                // noisy: row terms summed from the block's end back, the block-end terms of all its rows,
+                // and of dDelta~ . Delta~, a block-end term less a row term, the rows before
+                float x = xp + xb, e = xa, before = __shfl_up(xw, 1);
+                if ((lane & (nl - 1)) == 0) before = 0.f;
                 for (int o = 1; o < nl; o <<= 1) {
-                    const float y = __shfl_down(x, o);
+                    const float y = __shfl_down(x, o), w = __shfl_up(before, o);
                     if ((lane & (nl - 1)) + o < nl) x += y;
+                    if ((lane & (nl - 1)) >= o) before += w;
                     e += __shfl_xor(e, o);
                 }
                 if (lane < nvalid) {
-                    pn.dg[(long)lane * a.h_v] = (x + e) * inv;
+                    pn.dg[(long)lane * a.h_v] = (x + e + before) * inv;
                     pn.db[(long)lane * a.h_v] = sm.dB[lane] * inv;
                 }
             } else {
