@@ -625,8 +625,9 @@ static bool bwd_pairs(const bdgdn_fwd_desc_t *d) { return d->block > 32; }
 // several noisy blocks each (bwd_small.hpp): one unit per chunk instead of one padded unit and
 // one serial scan step per block.  At 1 x 4096 tokens, 16 heads, blocks of 4, the whole backward: 3.75 ms block by
 // block (noisy 1110 us, scan 1102, clean 832, seeds 683), 0.66 ms on chunks (187, 144, 171, 134).
-// The chunk's workspace (kSmallChunk positions a unit) is below the per-block one unless packed
-// documents are shorter than a chunk; where it does not fit the caller's, blocks run one by one.
+// A chunk takes 88 KB of workspace per v-head and a block 72, so that chunks fit the queried size but
+// where most of the sequences or documents are of one block (and their one chunk the larger); where
+// they do not fit the caller's, not in time segments either, blocks run one by one.
 constexpr int kSmallChunk = 32;
 static bool bwd_small(const bdgdn_fwd_desc_t *d)
 {
@@ -730,8 +731,8 @@ static bool seg_plan(const bdgdn_fwd_desc_t *d, const int32_t *cu_host, int segm
     return true;
 }
 // Workspace of the segmented backward: the checkpoints at segment starts 1 .. n_seg - 1, the
-// state-gradient carry (fp32 [seq][h_v][d_k][d_v] each), the segment tables, then the
-// per-block layout for segment 0's blocks.
+// state-gradient carry (fp32 [seq][h_v][d_k][d_v] each; none for a single segment), the segment
+// tables, then the per-block layout for segment 0's blocks.
 struct SegLayout {
     size_t ckpt, carry, tab;
     BwdLayout body;
@@ -743,7 +744,7 @@ static SegLayout seg_layout(const bdgdn_fwd_desc_t *d, const SegPlan &p, bool sm
     SegLayout l;
     l.ckpt = 0;
     l.carry = l.ckpt + up256((size_t)(p.n_seg - 1) * state);
-    l.tab = l.carry + up256(state);
+    l.tab = l.carry + (p.n_seg > 1 ? up256(state) : 0);
     const size_t tab_bytes = 2 * (size_t)p.n_seg * (nseq + 1) * sizeof(int);
     l.body = bwd_layout_units((size_t)p.max_units * d->h_v, d, l.tab + up256(tab_bytes), small);
     return l;

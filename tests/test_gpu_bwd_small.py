@@ -45,25 +45,36 @@ def _case(B, T, hqk, hv, L, lengths=None, out=torch.float32, gates=None):
     return run, desc, cu, ref
 
 
+def _on_chunks(workspace, T, cu, B):
+    """Whether a call ran on chunks in one pass: its segment table, the chunks of the sequences before
+    each one, is then what the workspace starts with."""
+    lens = [T] * B if cu is None else np.diff(cu.numpy())
+    table = np.concatenate([[0], np.cumsum([-(-int(x) // 32) for x in lens])])
+    return bool((workspace[:4 * len(table)].cpu().numpy().view(np.int32) == table).all())
+
+
 def _check(got, ref):
     for name in NAMES:
         e = rel_err(got[name], ref[name])
         assert e <= TOL["bf16"], f"{name}: {e:.2e}"
 
 
-@pytest.mark.parametrize("B,T,hqk,hv,L,lengths,out", [
-    (1, 32, 1, 1, 1, None, torch.float32),                     # one chunk, 32 noisy blocks
-    (1, 33, 1, 2, 2, None, torch.float32),                     # one position into a second chunk, grouped heads
-    (2, 100, 2, 2, 4, None, torch.bfloat16),                   # the last chunk one block, bf16 upstream gradients
-    (1, 95, 1, 4, 8, None, torch.float32),                     # a block short of its last position
-    (3, 48, 1, 1, 16, None, torch.float32),                    # half a chunk
-    (1, 203, 1, 2, 8, [40, 0, 8, 64, 91], torch.float32),      # documents across, inside and on chunks, an empty one
-    (1, 9, 1, 1, 16, None, torch.float32),                     # less than a block
+@pytest.mark.parametrize("B,T,hqk,hv,L,lengths,out,more", [
+    (1, 32, 1, 1, 1, None, torch.float32, 0),                     # one chunk, 32 noisy blocks
+    (1, 33, 1, 2, 2, None, torch.float32, 0),                     # one position into a second chunk, grouped heads
+    (2, 100, 2, 2, 4, None, torch.bfloat16, 0),                   # the last chunk one block, bf16 upstream gradients
+    (1, 95, 1, 4, 8, None, torch.float32, 0),                     # a block short of its last position
+    (3, 48, 1, 1, 16, None, torch.float32, 0),                    # half a chunk
+    (1, 203, 1, 2, 8, [40, 0, 8, 64, 91], torch.float32, 0),      # documents across, inside and on chunks, an empty one
+    (1, 9, 1, 1, 16, None, torch.float32, 1 << 16),               # less than a block: a larger workspace than queried
+    (1, 96, 1, 1, 16, [16] * 6, torch.float32, 1 << 18),          # documents of one block, the same
 ])
-def test_small_blocks_match_oracle(B, T, hqk, hv, L, lengths, out):
+def test_small_blocks_match_oracle(B, T, hqk, hv, L, lengths, out, more):
     print(f"small blocks B={B} T={T} h={hqk}/{hv} L={L} {lengths}", flush=True)
-    run, _, _, ref = _case(B, T, hqk, hv, L, lengths, out)
-    _check(run(), ref)
+    run, desc, cu, ref = _case(B, T, hqk, hv, L, lengths, out)
+    ws = torch.full((bd.bdgdn_bwd_train_workspace(desc) + more,), 255, dtype=torch.uint8, device="cuda")
+    _check(run(ws), ref)
+    assert _on_chunks(ws, T, cu, B)
 
 
 @pytest.mark.parametrize("L", [1, 4, 16])
@@ -105,4 +116,6 @@ def test_documents_shorter_than_a_chunk_keep_their_workspace():
     one by one in it."""
     run, desc, cu, ref = _case(1, 96, 1, 1, 16, [16] * 6)
     print("small blocks: documents of one block", flush=True)
-    _check(run(torch.empty(bd.bdgdn_bwd_train_workspace(desc), dtype=torch.uint8, device="cuda")), ref)
+    ws = torch.full((bd.bdgdn_bwd_train_workspace(desc),), 255, dtype=torch.uint8, device="cuda")
+    _check(run(ws), ref)
+    assert not _on_chunks(ws, 96, cu, 1)
