@@ -841,9 +841,13 @@ static int bwd_impl(const bdgdn_fwd_desc_t *desc, const void *q, const void *k, 
     if (!generic && n_more == 0 && bwd_small(desc)) {
         SegPlan cp;
         for (int K = 1; !small && seg_plan(&chunks, cu_seqlens_host, K, false, cp); ++K) {
-            small = (K == 1 || cp.n_seg > 1) && seg_layout(desc, cp, true).body.total <= workspace_bytes;
+            const SegLayout cl = seg_layout(desc, cp, true);
+            small = (K == 1 || cp.n_seg > 1) && cl.body.total <= workspace_bytes;
             if (small) seg_plan(&chunks, cu_seqlens_host, K, true, plan);
-            if (cp.seg_len <= 1) break;
+            // no finer segments, or none that could fit: the checkpoints, which grow with their number,
+            // are too large alone (a pass over the documents for each number up to a long document's
+            // chunks took 150 ms of host time with 8000 short ones beside it)
+            if (cp.seg_len <= 1 || cl.body.seeds > workspace_bytes) break;
         }
         segmented = segmented || small;
     }

@@ -2,6 +2,7 @@
 32 (one noisy view): against the fp64 oracle at the edges of a chunk, in time segments bit for
 bit, and the per-block schedule where packed documents are shorter than a chunk."""
 import math
+import time
 
 import numpy as np
 import pytest
@@ -119,3 +120,29 @@ def test_documents_shorter_than_a_chunk_keep_their_workspace():
     ws = torch.full((bd.bdgdn_bwd_train_workspace(desc),), 255, dtype=torch.uint8, device="cuda")
     _check(run(ws), ref)
     assert not _on_chunks(ws, 96, cu, 1)
+
+
+def test_short_documents_beside_a_long_one_are_planned_at_once():
+    """Chunks do not fit the queried workspace here in any number of segments: finding that out takes a
+    few passes over the documents, not one for every number of segments of the long one (over 50 ms)."""
+    lengths = [16] * 12000 + [6000 * 16]
+    T, L = sum(lengths), 16
+    cu = torch.tensor(np.concatenate([[0], np.cumsum(lengths)]), dtype=torch.int32)
+    gen = torch.Generator(device="cuda").manual_seed(0)
+    x = [torch.randn(1, T, 1, 128, generator=gen, device="cuda").mul_(0.1).bfloat16() for _ in range(3)]
+    gate = torch.full((1, T, 1), -0.05, device="cuda")
+    beta = torch.full((1, T, 1), 0.5, device="cuda")
+    do = torch.zeros(1, T, 1, 128, device="cuda")
+    ws = torch.empty(bd.bdgdn_bwd_train_workspace(bd.make_fwd_desc(x[0], x[2], block=L, num_seqs=len(lengths))),
+                     dtype=torch.uint8, device="cuda")
+    print("small blocks: many short documents and a long one", flush=True)
+    times = []
+    for _ in range(3):
+        torch.cuda.synchronize()
+        t = time.perf_counter()
+        bd.bdgdn_bwd_train(*x, gate, beta, *x, gate, beta, do, do, block=L, cu_seqlens=cu.cuda(), cu_seqlens_host=cu,
+                           workspace=ws)
+        times.append(time.perf_counter() - t)
+    torch.cuda.synchronize()
+    assert not _on_chunks(ws, T, cu, 1)
+    assert min(times) < 0.02, times
