@@ -580,21 +580,26 @@ template <typename Od, bool SMALL> __global__ void __launch_bounds__(512, 4) bdg
             settle(kds[tm]);
         }
         reread();
-        // ---- the solve (wave 0) and Gram tiles (waves 1 .. 7): K K^T, P = (Q K^T) o Mc
+        // ---- the solve (wave 0) and Gram tiles: K K^T (waves 1 .. 3), P = (Q K^T) o Mc (waves 4 .. 7, which
+        // keep their tile of Q K^T in fp32 for its gate terms: at g = -8 an entry of P is below fp16's
+        // normal range, and with it dg was 7e-4 of its 2-norm off, where 3e-4 are left)
+        const int m0 = 16 * ((wave >> 1) & 1), n0 = 16 * (wave & 1);
+        f32x4 qk = z;
         if (wave == 0) {
             solve_block(sm.K, sm.G2, sm.bet, sm.Mh, lane);
-        } else {
-            for (int e = wave - 1; e < 8; e += 7) {
-                const int m0 = 16 * ((e >> 1) & 1), n0 = 16 * (e & 1), i = n0 + rr;
-                const f32x4 c = tile_mma<_Float16, DD>(z, (e < 4 ? sm.K : sm.Q) + m0 * LDH, LDH, sm.K + n0 * LDH, LDH, lane);
+        } else if (wave < 4) {
+            for (int e = wave - 1; e < 4; e += 3) {
+                const int mk = 16 * (e >> 1), nk = 16 * (e & 1);
+                const f32x4 c = tile_mma<_Float16, DD>(z, sm.K + mk * LDH, LDH, sm.K + nk * LDH, LDH, lane);
 #pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    const int t = m0 + 4 * g4 + j;
-                    if (e < 4)
-                        sm.KK[t * LDF + i] = c[j];
-                    else
-                        sm.Ph[t * LDM + i] = (_Float16)(i <= t ? c[j] * ex(sm.G[t] - sm.G[i]) : 0.f);
-                }
+                for (int j = 0; j < 4; ++j) sm.KK[(mk + 4 * g4 + j) * LDF + nk + rr] = c[j];
+            }
+        } else {
+            qk = tile_mma<_Float16, DD>(z, sm.Q + m0 * LDH, LDH, sm.K + n0 * LDH, LDH, lane);
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const int t = m0 + 4 * g4 + j, i = n0 + rr;
+                sm.Ph[t * LDM + i] = (_Float16)(i <= t ? qk[j] * ex(sm.G[t] - sm.G[i]) : 0.f);
             }
         }
         reread();
@@ -643,22 +648,23 @@ template <typename Od, bool SMALL> __global__ void __launch_bounds__(512, 4) bdg
             }
         }
         __syncthreads();
-        // ---- E = dO Delta^T (waves 0 .. 3): the gradient of Q K^T into dPh, the gates of Mc; dT =
-        // dDelta R^T (waves 4 .. 7); products with S0^T and dS^T
+        // ---- E = dO Delta^T (waves 4 .. 7): the gradient of Q K^T into dPh, the gates of Mc; dT =
+        // dDelta R^T (waves 0 .. 3); products with S0^T and dS^T
         {
-            const int m0 = 16 * ((wave >> 1) & 1), n0 = 16 * (wave & 1), i = n0 + rr;
-            const bool lo = wave < 4;
-            const f32x4 e = tile_mma<_Float16, DD>(z, (lo ? sm.dO : sm.dDl) + m0 * LDH, LDH, (lo ? sm.Dl : sm.R) + n0 * LDH,
+            const int i = n0 + rr;
+            const bool hi = wave >= 4;
+            const f32x4 e = tile_mma<_Float16, DD>(z, (hi ? sm.dO : sm.dDl) + m0 * LDH, LDH, (hi ? sm.Dl : sm.R) + n0 * LDH,
                                                    LDH, lane);
             float colw = 0.f;
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
                 const int t = m0 + 4 * g4 + j;
-                if (lo) {
+                if (hi) {
+                    const float d = i <= t ? s * e[j] * ex(sm.G[t] - sm.G[i]) : 0.f;
                     // the diagonal, in the row and the column sum of one position, is in neither
-                    const float w = i < t ? s * e[j] * (float)sm.Ph[t * LDM + i] : 0.f;
-                    sm.dPh[t * LDM + i] = (_Float16)(i <= t ? s * e[j] * ex(sm.G[t] - sm.G[i]) : 0.f);
-                    if (wave >> 1)
+                    const float w = i < t ? d * qk[j] : 0.f;
+                    sm.dPh[t * LDM + i] = (_Float16)d;
+                    if (m0)
                         rowg[1][j] += w;
                     else
                         rowg[0][j] += w;
@@ -667,7 +673,7 @@ template <typename Od, bool SMALL> __global__ void __launch_bounds__(512, 4) bdg
                     sm.dT[t * LDF + i] = e[j];
                 }
             }
-            if (lo) {
+            if (hi) {
                 colw += __shfl_xor(colw, 16);
                 colw += __shfl_xor(colw, 32);
                 if (g4 == 0) lds_add(&sm.part[wave][i], -colw);

@@ -334,12 +334,14 @@ template <typename Od> __global__ void __launch_bounds__(512) bdgdn_bwd_small_ke
             const f32x4 f = tile_mma<_Float16, DD>(z, (lo ? sm.dOn : sm.Bn) + m0 * LDH, LDH, sm.Dl + n0 * LDH, LDH, lane);
             const f32x4 e = tile_mma<_Float16, DD>(z, (lo ? sm.dOn : sm.dDn) + m0 * LDH, LDH,
                                                    (lo ? Dln : sm.Rn) + n0 * LDH, LDH, lane);
+            // the Gram entries of W again in fp32: at g = -8 those of Nq and Nk are below fp16's normal range
+            const f32x4 gr = tile_mma<_Float16, DD>(z, (lo ? sm.Qn : sm.Kn) + m0 * LDH, LDH, sm.K + n0 * LDH, LDH, lane);
             float colw = 0.f;
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
                 const int t = m0 + 4 * g4 + j;
                 const float m = i < (t & ~(nl - 1)) ? ex(sm.Gp[t] - sm.G[i]) : 0.f, x = lo ? sm.sg[t] * f[j] : f[j];
-                float w = x * (float)(lo ? sm.Nq : sm.Nk)[t * LDM + i];
+                float w = x * m * gr[j];
                 if (i + 1 == (t & ~(nl - 1))) {
                     sm.pD[wave >> 2][t] = w;
                     w = 0.f;

@@ -63,3 +63,11 @@ def test_noisy_blocks_in_a_chunk_round_once_per_factor(L):
     noisy keys' own) and smaller ones.  Rounding a = s gamma~_n dO~ to fp16 was a fourth."""
     err = _errors(L, [-4.0] * 4, [None] * 4, False)
     assert err["dv"] <= 1.9 * ONE
+
+
+@pytest.mark.parametrize("L", [1, 4, 16, 32, 64])
+def test_clean_dg_keeps_entries_of_the_decays_order(L):
+    """dg at clean gates of -8, where every term is of order exp(-8): Delta, dDelta and R~ are rounded
+    once each, and the terms' Gram entries not at all (in fp16 they were below its normal range)."""
+    err = _errors(L, [-8.0] * 4, [None] * 4, True, T=128)
+    assert err["dg"] <= 2.5 * ONE
