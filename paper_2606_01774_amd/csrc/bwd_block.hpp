@@ -628,7 +628,7 @@ template <typename Od, bool SMALL> __global__ void __launch_bounds__(512, 4) bdg
                     const float w = ex(Ge - sm.G[t]) * kds[tm][j];
                     d[j] += w;
                     // the last position's own term would be taken off itself
-                    rowg[tm][j] = t < NP - 1 ? -w * (float)dl[j] : 0.f;
+                    rowg[tm][j] = t < nvalid - 1 ? -w * (float)dl[j] : 0.f;
                     dlast -= rowg[tm][j];
                 }
                 if constexpr (SMALL)

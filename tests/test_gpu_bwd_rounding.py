@@ -19,9 +19,9 @@ KEYS = ("q", "k", "v", "g", "beta")
 ONE = 2.0 ** -11 / math.sqrt(3) * math.sqrt(0.375 / math.log(2))
 
 
-def _errors(L, clean, noisy, with_clean, T=96, seeds=4):
+def _errors(L, clean, noisy, with_clean, T=96, seeds=4, with_dht=False):
     """Relative 2-norm error of every gradient over all heads and seeds; the clean readout's
-    upstream gradient zero unless with_clean."""
+    upstream gradient zero unless with_clean, that of the final state without with_dht."""
     H, num, den = len(clean), {}, {}
     for seed in range(seeds):
         inp = W.make_custom_train(1, T, H, H, 128, 128, "bf16", seed=300 + seed)
@@ -31,11 +31,12 @@ def _errors(L, clean, noisy, with_clean, T=96, seeds=4):
                    for _ in range(2))
         if not with_clean:
             do = torch.zeros_like(do)
+        dht = torch.from_numpy(0.1 * rng.standard_normal((1, H, 128, 128)).astype(np.float32)) if with_dht else None
         got = bd.bdgdn_bwd_train(*[inp[k].cuda() for k in KEYS], *[inp[k + "n"].cuda() for k in KEYS], do.cuda(),
-                                 don.cuda(), block=L, want_dh0=True)
+                                 don.cuda(), block=L, dht=None if dht is None else dht.cuda(), want_dh0=True)
         torch.cuda.synchronize()
         ref = oracle.bwd_train(*[inp[k] for k in KEYS], *[inp[k + "n"] for k in KEYS], do, don, block=L,
-                               scale=1 / math.sqrt(128))
+                               scale=1 / math.sqrt(128), dht=dht)
         for name, x in ref.items():
             if not x.any():
                 continue   # dq without a clean readout
@@ -70,4 +71,12 @@ def test_clean_dg_keeps_entries_of_the_decays_order(L):
     """dg at clean gates of -8, where every term is of order exp(-8): Delta, dDelta and R~ are rounded
     once each, and the terms' Gram entries not at all (in fp16 they were below its normal range)."""
     err = _errors(L, [-8.0] * 4, [None] * 4, True, T=128)
+    assert err["dg"] <= 2.5 * ONE
+
+
+@pytest.mark.parametrize("L", [4, 7, 32, 64])
+def test_clean_dg_of_a_short_last_block(L):
+    """The same with a last block of fewer positions than its padding (of 7 all are): the state
+    gradient's term on the last position, of order one, would be added to a sum and taken off again."""
+    err = _errors(L, [-8.0] * 4, [None] * 4, True, T=86, with_dht=True)
     assert err["dg"] <= 2.5 * ONE
