@@ -279,14 +279,15 @@ size_t bdgdn_bwd_train_workspace_segmented(const bdgdn_fwd_desc_t *desc, const i
  *                        chip; one more clean-scan pass over all but the last segment and
  *                        more, smaller launches); BDGDN_ERR_WORKSPACE if none fits
  * Every gradient row is overwritten.  bf16 inputs with d_k = d_v = 128 and blocks of at
- * most 32 positions run the block-form kernels (blocks of 1, 2, 4, 8 or 16 positions with one
- * noisy view on clean chunks of 32 that hold several, segmented by chunks, wherever that fits
- * the workspace); fp32 inputs (blocks of at most 32), d_k or
+ * most 32 positions, or an even 34 .. 64, run the block-form kernels (blocks of 1, 2, 4, 8 or
+ * 16 positions with one noisy view on clean chunks of 32 that hold several, segmented by
+ * chunks, wherever that fits the workspace, else block by block, which rounds differently);
+ * fp32 inputs (blocks of at most 32), d_k or
  * d_v of 64, and odd bf16 blocks of 33 .. 63 positions run the per-step fp32 backward (at
  * most 512 packed documents and four views): all blocks in parallel between two serial walks
  * of the clean state and its gradient, or, with less workspace than two states per (block,
- * v-head), one wave per (chain, 16-column tile) walking the steps backwards from strided
- * clean checkpoints.  Anything else is BDGDN_ERR_UNSUPPORTED.  The block-form kernels and the
+ * v-head) or where these are over 2 GiB, one wave per (chain, 16-column tile) walking the
+ * steps backwards from strided clean checkpoints.  Anything else is BDGDN_ERR_UNSUPPORTED.  The block-form kernels and the
  * parallel per-step ones are deterministic, grouped value heads included (dq, dk of a q/k
  * head summed over its v-heads in a fixed order).  The serial per-step walk sums dq, dk, dg
  * and dbeta over its column tiles with floating-point atomics (summation order not fixed).

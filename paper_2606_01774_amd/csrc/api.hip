@@ -751,8 +751,8 @@ static SegLayout seg_layout(const bdgdn_fwd_desc_t *d, const SegPlan &p, bool sm
 }
 
 // Shapes outside the block-form kernels run the per-step fp32 backward: parallel over blocks
-// (bwd_steps.hip) given its two states per (block, v-head), else, with less workspace, the
-// serial walk from strided checkpoints (bwd_generic.hip).
+// (bwd_steps.hip) given its two states per (block, v-head), else, with less workspace or where
+// these are over kStepsMaxBytes, the serial walk from strided checkpoints (bwd_generic.hip).
 static bool bwd_generic_ok(const bdgdn_fwd_desc_t *d, int n_views)
 {
     return !bwd_shape_ok(d) && d->num_seqs <= kMaxOrder &&

@@ -760,7 +760,9 @@ size_t bwd_steps_workspace(long total_blocks, int h_v, int dk, int dv)
 // The line between this schedule and the serial walk is workspace alone: at every size
 // measured this one is faster (7 x at 3 x 63 positions in blocks of 16, 27 x at 1 x 256 in
 // blocks of 16, 38 x at 2 x 369 in blocks of 4), so it runs whenever the caller gives it its
-// two states per (block, v-head).
+// two states per (block, v-head), but where these are more than kStepsMaxBytes, the most that a
+// call asks for here (d = 128, 16 v-heads, blocks of 16: past 16384 positions): there the
+// walk runs whatever the workspace.
 hipError_t launch_bwd_steps(bool f32_in, bool f32_out, const GenBwdCall &c, hipStream_t s)
 {
     StepArgs a = {};

@@ -347,6 +347,12 @@ def test_bwd_train_validation_and_workspace():
         d = _desc(**kw)
         assert lib.bdgdn_bwd_train_workspace(ctypes.byref(d)) > 0, kw
         assert _bwd(d) == bd.BDGDN_ERR_WORKSPACE, kw   # every check passes but the workspace
+    # two states per (block, v-head) for the schedule parallel over blocks, where these are at most 2 GiB
+    # (here 1024 blocks of 16 heads), and what the walk needs beyond
+    long = dict(seqlen=16384, h_v=16, block=16, dtype=bd.BDGDN_F32, out_dtype=bd.BDGDN_F32)
+    assert lib.bdgdn_bwd_train_workspace(ctypes.byref(_desc(**long))) == 2 << 30
+    walk = (1025 // 8 + 1) * 16 * 128 * 128 * 4 + 16 * 8 * 8 * 128 * 16 * 4
+    assert lib.bdgdn_bwd_train_workspace(ctypes.byref(_desc(**dict(long, seqlen=16385)))) == walk
     assert _bwd(_desc(h_v=3)) == bd.BDGDN_ERR_INVALID_ARG
     assert _bwd(ok, null_grad=True) == bd.BDGDN_ERR_INVALID_ARG
     assert _bwd(ok, ws=None, ws_bytes=0) == bd.BDGDN_ERR_WORKSPACE
