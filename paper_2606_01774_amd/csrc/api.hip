@@ -623,8 +623,9 @@ static bool bwd_shape_ok(const bdgdn_fwd_desc_t *d)
 static bool bwd_pairs(const bdgdn_fwd_desc_t *d) { return d->block > 32; }
 // Blocks of 1, 2, 4, 8 or 16 positions with one noisy view run on clean chunks of 32 that hold
 // several noisy blocks each (bwd_small.hpp): one unit per chunk instead of one padded unit and
-// one serial scan step per block.  At 1 x 4096 tokens, 16 heads, blocks of 4, the whole backward: 3.75 ms block by
-// block (noisy 1110 us, scan 1102, clean 832, seeds 683), 0.66 ms on chunks (187, 144, 171, 134).
+// one serial scan step per block.  At 1 x 4096 tokens, 16 heads, blocks of 4, the whole backward: 2.49 ms block by
+// block (noisy 621 us, scan 665, clean 490, seeds 699), 0.55 ms on chunks (189, 90, 112, 133); in blocks of
+// 16, the longest that share a chunk, 0.70 ms (173, 174, 146, 192) and 0.55 ms.
 // A chunk takes 88 KB of workspace per v-head and a block 72, so that chunks fit the queried size but
 // where most of the sequences or documents are of one block (and their one chunk the larger); where
 // they do not fit the caller's, not in time segments either, blocks run one by one.

@@ -10,9 +10,11 @@
 // turned over through 512 bytes of its own.  Everything that needs only a wave's 16 columns
 // runs without a barrier; the noisy block-end gradient s Q~^T dO~ is never formed, K~ dS~
 // coming from the Gram tiles K~ Q~^T.  At 4 x 4096 tokens, 16 heads, blocks of 32 (8192
-// units): noisy 640 -> 456 us, clean 520 -> 358 us, against one workgroup of 160 KB per CU with
+// units): noisy 640 -> 456 us, clean 520 -> 358 us (425 and 340 on the fastest of the boxes they were
+// measured on), against one workgroup of 160 KB per CU with
 // both states in LDS.  Registers are what the form hangs on: with 17 of them spilled the
-// kernels wrote 300 and 270 MB of scratch and took 490 and 416 us, hence settle() and reread().
+// kernels wrote 300 and 270 MB of scratch and took 490 and 416 us, hence settle() and reread();
+// one is still spilled where the noisy kernel prepares the clean block too (8 bytes a lane).
 
 // a 16 x 32 by 32 x 16 product from operand quads over k = 0 .. 15 and 16 .. 31 (one
 // 16x16x32 step: A and B agree on which k each slot holds)

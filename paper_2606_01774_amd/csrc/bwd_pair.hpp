@@ -29,7 +29,7 @@
 // its 430 KB of HBM traffic are 22 at a large copy's rate, which do not overlap the barriers
 // (9.5 k clocks to the end of the solves, 10 k for the columns' products and the clean
 // preparation, 10 k for the tiles over the columns).  At 2 x 16384 tokens, 32 v-heads over 16
-// q/k heads, blocks of 64 (16384 units): 3300 -> 1976 us against one workgroup of eight waves
+// q/k heads, blocks of 64 (16384 units): 3300 -> 1990 us against one workgroup of eight waves
 // forming S~1, S~2 and their gradients.  Loading the next unit's inputs during the last phases
 // from a persistent grid took 2040 us (they don't fit beside the last phases: nine registers
 // spilled, and waves stall at the issue of loads).

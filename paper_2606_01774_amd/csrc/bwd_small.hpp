@@ -28,8 +28,8 @@
 // and dg with its shares, and runs the clean preparation (the dh-independent part of dS0, U K)
 // with dDelta's share XD included; the clean pass then adds to dk and dg.
 //
-// Measured at 2048 (chunk, head) units (1 x 4096 tokens, 16 heads), nl = 4: 187 us, against
-// 1110 us for 16384 padded units of the per-block kernel.
+// Measured at 2048 (chunk, head) units (1 x 4096 tokens, 16 heads), nl = 4: 189 us, against
+// 621 us for 16384 padded units of the per-block kernel (1110 us before that ran twice on a CU).
 // Bound by the latency of its phases: one workgroup per CU (159 KB of LDS), persistent, the
 // next unit's rows in flight during the second half of each unit.  Everything that needs only
 // a wave's own 16 columns runs without a barrier from the solves to the chunk's c term.

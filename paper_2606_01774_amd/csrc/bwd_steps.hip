@@ -31,9 +31,10 @@
 // order (deterministic, no atomics; the v-heads of a q/k head are added in turn).
 //
 // What bounds it: the instructions of the two serial walks, one wave in order (0.11 us per
-// step forwards, 0.15 us backwards), and in the block kernels three walks of a block each.
-// Measured at 1 x 256 + 256 tokens, 2 heads, d = 64, L = 16 in fp32: states 28 us, noisy
-// 31 us, reverse 38 us, clean 29 us; the one-wave walk of bwd_generic.hip, whose steps waited
+// step forwards, 0.15 us backwards), and in the block kernels a walk of a block each way and the
+// states rebuilt in between.
+// Measured at 1 x 256 + 256 tokens, 2 heads, d = 64, L = 16 in fp32: states 28 to 32 us by box, noisy
+// 27 us, reverse 38 us, clean 25 us; the one-wave walk of bwd_generic.hip, whose steps waited
 // for loads and for two butterflies over the columns each, 4.04 ms.  The walks' 4-column
 // tiles and per-chunk row pointers: 41 + 53 us with a 64-bit row product per position.
 #include "bwd.hpp"
