@@ -112,7 +112,7 @@ __device__ __forceinline__ float back_sum32(float x, int lane)
 // Cumulative log-gates of a block from the gate of each lane (wave 0 or 1, lanes 0 .. 31).
 __device__ __forceinline__ float cum_to_lds(float g, float *G, float *G2, float *gam, int lane)
 {
-    const float x = ut::scan32(lane < NP ? g : 0.f, lane);
+    const float x = ut::scan32(lane < NP ? ut::gate_floor(g) : 0.f, lane);
     if (lane < NP) {
         G[lane] = x;
         G2[lane] = x * kLog2e;

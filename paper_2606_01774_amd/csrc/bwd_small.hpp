@@ -120,9 +120,9 @@ template <typename Od> __global__ void __launch_bounds__(512) bdgdn_bwd_small_ke
         store_seed(sm.S0, in.seed, tid);
         if (tid < NP) {
             sm.bet[tid] = in.c.b;
-            sm.G[tid] = in.c.g;
+            sm.G[tid] = ut::gate_floor(in.c.g);
             sm.betn[tid] = in.n.b;
-            sm.Gn[tid] = in.n.g;
+            sm.Gn[tid] = ut::gate_floor(in.n.g);
         }
         if (tid < kWaves * NP) {
             sm.part[tid / NP][tid % NP] = 0.f;

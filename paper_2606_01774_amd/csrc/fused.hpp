@@ -370,6 +370,7 @@ struct Fused {
                                              const ut::Consts &us_, int nl) const
     {
         float *Gs = us(STREAM), *Bs = Gs + 64;   // cumulative log2-gates, beta
+        if constexpr (STATES) gv = ut::gate_floor(gv);   // chunks of small blocks sum over more of them
         const float x = ut::scan32(lane < LP ? gv * kLog2e : 0.f, lane);
         const float gl = ut::lane_value(x, LP - 1);
         Gs[lane] = x;

@@ -24,6 +24,10 @@ __device__ __forceinline__ float lane_value(float v, int l)
 {
     return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), l));
 }
+// A log-gate as it enters a cumulative sum: below -128 (exp is 0 in fp32 from -104 on) it is -128,
+// since the rounding of a larger one would stay in the differences of all the positions after it.
+// NaN stays NaN.
+__device__ __forceinline__ float gate_floor(float g) { return g < -128.f ? -128.f : g; }
 // Inclusive prefix sum over lanes 0 .. 31: shifts by 1, 2, 4, 8 inside each 16-lane row,
 // then the total of row 0 carried into row 1.
 __device__ __forceinline__ float scan32(float x, int lane)

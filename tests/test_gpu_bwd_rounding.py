@@ -38,12 +38,12 @@ def _errors(L, clean, noisy, with_clean, T=96, seeds=4, with_dht=False):
         ref = oracle.bwd_train(*[inp[k] for k in KEYS], *[inp[k + "n"] for k in KEYS], do, don, block=L,
                                scale=1 / math.sqrt(128), dht=dht)
         for name, x in ref.items():
-            if not x.any():
-                continue   # dq without a clean readout
             axes = tuple(i for i in range(x.ndim) if i != (1 if name == "dh0" else 2))
             d = got[name].double().cpu().numpy() - x
-            scale = (x * x).mean(axis=axes)   # each head by its own size
-            num[name] = num.get(name, 0) + ((d * d).mean(axis=axes) / scale).mean() / seeds
+            scale, e = (x * x).mean(axis=axes), (d * d).mean(axis=axes)
+            if not scale.all():
+                continue   # zero: dq without a clean readout, dh0 behind a reset
+            num[name] = num.get(name, 0) + (e / scale).mean() / seeds   # each head by its own size
     err = {name: math.sqrt(x) for name, x in num.items()}
     print(f"L={L}", {name: f"{x:.2e}" for name, x in err.items()}, flush=True)
     return err
@@ -80,3 +80,13 @@ def test_clean_dg_of_a_short_last_block(L):
     gradient's term on the last position, of order one, would be added to a sum and taken off again."""
     err = _errors(L, [-8.0] * 4, [None] * 4, True, T=86, with_dht=True)
     assert err["dg"] <= 2.5 * ONE
+
+
+@pytest.mark.parametrize("reset", [-1e4, -1e7])
+@pytest.mark.parametrize("L", [1, 4, 16, 32, 64])
+def test_a_gate_of_any_size_costs_the_others_nothing(L, reset):
+    """One position in sixteen forgets everything, by whatever gate: the decays of the others come from
+    differences of cumulative gates, in which the large one's rounding (0.5 at -1e7) must not stay."""
+    err = _errors(L, [("single", reset)] * 2, [None, ("single", reset)], True)
+    for name in ("dq", "dk", "dv", "dbeta", "dqn", "dkn", "dvn", "dbetan"):
+        assert err[name] <= 4 * ONE, (name, err[name])
