@@ -281,7 +281,8 @@ size_t bdgdn_bwd_train_workspace_segmented(const bdgdn_fwd_desc_t *desc, const i
  * Every gradient row is overwritten.  bf16 inputs with d_k = d_v = 128 and blocks of at
  * most 32 positions, or an even 34 .. 64, run the block-form kernels (blocks of 1, 2, 4, 8 or
  * 16 positions with one noisy view on clean chunks of 32 that hold several, segmented by
- * chunks, wherever that fits the workspace, else block by block, which rounds differently);
+ * chunks, where a chain saves seven steps by them or they halve more units than the chip has
+ * CUs, and where that fits the workspace, else block by block, which rounds differently);
  * fp32 inputs (blocks of at most 32), d_k or
  * d_v of 64, and odd bf16 blocks of 33 .. 63 positions run the per-step fp32 backward (at
  * most 512 packed documents and four views): all blocks in parallel between two serial walks

@@ -626,8 +626,8 @@ static bool bwd_pairs(const bdgdn_fwd_desc_t *d) { return d->block > 32; }
 // one serial scan step per block.  At 1 x 4096 tokens, 16 heads, blocks of 4, the whole backward: 2.49 ms block by
 // block (noisy 621 us, scan 665, clean 490, seeds 699), 0.55 ms on chunks (189, 90, 112, 133); in blocks of
 // 16, the longest that share a chunk, 0.70 ms (173, 174, 146, 192) and 0.55 ms.
-// A chunk takes 88 KB of workspace per v-head and a block 72, so that chunks fit the queried size but
-// where most of the sequences or documents are of one block (and their one chunk the larger); where
+// A chunk takes 88 KB of workspace per v-head and a block 72, so that chunks fit the queried size wherever
+// they pay (chunks_pay) but where many documents of one block lie beside longer ones; where
 // they do not fit the caller's, not in time segments either, blocks run one by one.
 constexpr int kSmallChunk = 32;
 static bool bwd_small(const bdgdn_fwd_desc_t *d)
@@ -730,6 +730,18 @@ static bool seg_plan(const bdgdn_fwd_desc_t *d, const int32_t *cu_host, int segm
         }
     }
     return true;
+}
+// Whether small blocks run on chunks.  Where every unit has a CU, the chunks' kernels take 9 us more, and
+// each step of the seeds and the scan that they save on the longest chain gives 1.4: the whole backward
+// block by block and on chunks, 1 sequence, 16 heads, 8 blocks of 16 (4 steps saved) 56 and 62 us, 16 of
+// them (8 saved) 70 and 72, 16 blocks of 4 (14 saved) 67 and 56.  Beyond, they pay by work, if they halve
+// the units: 64 sequences, 2 q/k heads of 2, 3 blocks of 16 (384 units, 256 on chunks) 138 and 147 us, 3
+// blocks of 4 (384, 128 on chunks) 132 and 114.  Over 200 such shapes of 2 to 16 blocks the rule is
+// within 4 % of the faster way.
+static bool chunks_pay(const SegPlan &blocks, const SegPlan &chunks, int h_qk)
+{
+    return blocks.seg_len - chunks.seg_len >= 7 ||
+           (blocks.max_units * h_qk > 256 && blocks.max_units >= 2 * chunks.max_units);
 }
 // Workspace of the segmented backward: the checkpoints at segment starts 1 .. n_seg - 1, the
 // state-gradient carry (fp32 [seq][h_v][d_k][d_v] each; none for a single segment), the segment
@@ -839,8 +851,9 @@ static int bwd_impl(const bdgdn_fwd_desc_t *desc, const void *q, const void *k, 
     // units numbered by the segment tables too) whose workspace fits
     const bdgdn_fwd_desc_t chunks = small_chunks(desc);
     bool small = false;
-    if (!generic && n_more == 0 && bwd_small(desc)) {
-        SegPlan cp;
+    SegPlan bp, cp;   // of one segment
+    if (!generic && n_more == 0 && bwd_small(desc) && seg_plan(desc, cu_seqlens_host, 1, false, bp) &&
+        seg_plan(&chunks, cu_seqlens_host, 1, false, cp) && chunks_pay(bp, cp, desc->h_qk)) {
         for (int K = 1; !small && seg_plan(&chunks, cu_seqlens_host, K, false, cp); ++K) {
             const SegLayout cl = seg_layout(desc, cp, true);
             small = (K == 1 || cp.n_seg > 1) && cl.body.total <= workspace_bytes;

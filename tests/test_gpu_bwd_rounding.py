@@ -19,7 +19,7 @@ KEYS = ("q", "k", "v", "g", "beta")
 ONE = 2.0 ** -11 / math.sqrt(3) * math.sqrt(0.375 / math.log(2))
 
 
-def _errors(L, clean, noisy, with_clean, T=96, seeds=4, with_dht=False):
+def _errors(L, clean, noisy, with_clean, T=256, seeds=4, with_dht=False):
     """Relative 2-norm error of every gradient over all heads and seeds; the clean readout's
     upstream gradient zero unless with_clean, that of the final state without with_dht."""
     H, num, den = len(clean), {}, {}
@@ -70,7 +70,7 @@ def test_noisy_blocks_in_a_chunk_round_once_per_factor(L):
 def test_clean_dg_keeps_entries_of_the_decays_order(L):
     """dg at clean gates of -8, where every term is of order exp(-8): Delta, dDelta and R~ are rounded
     once each, and the terms' Gram entries not at all (in fp16 they were below its normal range)."""
-    err = _errors(L, [-8.0] * 4, [None] * 4, True, T=128)
+    err = _errors(L, [-8.0] * 4, [None] * 4, True)
     assert err["dg"] <= 2.5 * ONE
 
 
